@@ -299,9 +299,8 @@ sem_status sem_pcg_solve_noalloc(sem_handle *h, const sem_solve_opts *opts,
 /* Batches of independent solves of the system of section 4.2.2 (uneven
  * sizes, orders N in {3, 5, 7} may be mixed, or any single N).  A batch references existing handles (which
  * must outlive it) and owns its work lists, per-solve device scalars and
- * captured graphs.  One CG iteration of the whole batch is six launches of
- * persistent kernels over (solve, element tile) and (solve, node chunk)
- * work items, captured once in a HIP graph and replayed check_every
+ * captured graphs.  One CG iteration of the whole batch is two to five launches
+ * of kernels over (solve, element tile) and (solve, node chunk) work items, captured once in a HIP graph and replayed check_every
  * iterations at a time; finished solves drop out on the device.  A solve
  * gives bit-identical results alone (sem_pcg_solve) or inside any batch.
  * A batch of more than one solve needs meshes without a mass term

@@ -33,7 +33,8 @@
 // workgroup, the standalone operator) and k_bax (persistent workgroups
 // walking a list of (solve, element tile) items of a batch of independent
 // solves with mixed orders; one launch applies the operators of all solves,
-// and stores every element's energy p_e^T w_e for the solvers' (p, A p)).
+// inside CG to the new direction p' = z + beta p formed at the gather
+// (cg_dir.h), and stores every element's energy p'_e^T w_e for (p', A p')).
 #include "ax_tile.h"
 
 namespace sem {
@@ -41,18 +42,14 @@ namespace sem {
 // ---------------------------------------------------------------------------
 // standalone operator: one tile per workgroup
 // ---------------------------------------------------------------------------
-template <int N1, class TU, class TG, class TW, class TC, bool GATHER, bool NTW,
-          bool MASS>
+template <int N1, class TU, class TG, class TW, class TC, bool MASS>
 __global__ void __launch_bounds__((OpShape<N1, sizeof(TC)>::THREADS))
     k_ax(int64_t E, const TC *__restrict__ D, const TG *__restrict__ G,
-         const TU *__restrict__ u, TW *__restrict__ w,
-         const Box *__restrict__ box, const int32_t *__restrict__ stop,
-         const TG *__restrict__ H) {
+         const TU *__restrict__ u, TW *__restrict__ w, const TG *__restrict__ H) {
   using S = OpShape<N1, sizeof(TC)>;
   __shared__ __align__(16) TC smem[lds_words<N1, TC>(S::EPB)];
-  if (stop != nullptr && *stop != 0) return;  // uniform: solver finished
-  ax_tile<N1, S::EPB, TU, TG, TW, TC, GATHER, NTW, MASS, S::NTG, false, S::PRED>(
-      threadIdx.x, (int64_t)blockIdx.x * S::EPB, E, D, G, u, w, box, smem, H);
+  ax_tile<N1, S::EPB, TU, TG, TW, TC, false, true, MASS, S::NTG, false, S::PRED>(
+      threadIdx.x, (int64_t)blockIdx.x * S::EPB, E, D, G, u, w, nullptr, smem, H);
 }
 
 template <int N1, class TU, class TG, class TW, class TC>
@@ -63,15 +60,13 @@ static void launch_nt(int64_t E, const void *D, const void *G, const void *H,
   if (blocks == 0) return;
   const dim3 grid((unsigned)blocks), block(S::THREADS);
   if (H != nullptr)
-    hipLaunchKernelGGL((k_ax<N1, TU, TG, TW, TC, false, true, true>), grid, block,
-                       0, s, E, (const TC *)D, (const TG *)G, (const TU *)u,
-                       (TW *)w, (const Box *)nullptr, (const int32_t *)nullptr,
+    hipLaunchKernelGGL((k_ax<N1, TU, TG, TW, TC, true>), grid, block, 0, s, E,
+                       (const TC *)D, (const TG *)G, (const TU *)u, (TW *)w,
                        (const TG *)H);
   else
-    hipLaunchKernelGGL((k_ax<N1, TU, TG, TW, TC, false, true, false>), grid,
-                       block, 0, s, E, (const TC *)D, (const TG *)G,
-                       (const TU *)u, (TW *)w, (const Box *)nullptr,
-                       (const int32_t *)nullptr, (const TG *)nullptr);
+    hipLaunchKernelGGL((k_ax<N1, TU, TG, TW, TC, false>), grid, block, 0, s, E,
+                       (const TC *)D, (const TG *)G, (const TU *)u, (TW *)w,
+                       (const TG *)nullptr);
 }
 
 template <int N1>
@@ -110,36 +105,50 @@ template <int BS, int N1> struct BTile {
   static constexpr int EPB = (BS / (N1 * N1)) > 0 ? BS / (N1 * N1) : 1;
 };
 
-template <int BS, class TV, class TG, class TC, int N1>
-__device__ __forceinline__ void bax_one(const BatchSolve &sd, int64_t e0,
-                                        int src, int dst, TC *smem) {
+// the direction arguments of a solve of the batch: the old direction in, the
+// new one out; par selects which of VP and VW is which
+template <class TV>
+__device__ inline DirArgs<TV> batch_dir(const BatchSolve &sd, CgState *st, const BaxDir &bd,
+                                        int s) {
+  auto v = [&](int i) { return (TV *)(sizeof(TV) == 8 ? sd.v64[i] : sd.v32[i]); };
+  return {v(bd.par ? VW : VP), v(bd.par ? VP : VW), st + s, bd.part, bd.stride,
+          bd.vbeg[s],          bd.vbeg[s + 1]};
+}
+
+template <int BS, class TV, class TG, class TC, int DIR, int N1>
+__device__ __forceinline__ void bax_one(const BatchSolve &sd, int64_t e0, int src,
+                                        const DirArgs<TV> &dir, TC *smem) {
   const TV *u = (const TV *)(sizeof(TV) == 8 ? sd.v64[src] : sd.v32[src]);
-  TV *w = (TV *)(sizeof(TV) == 8 ? sd.v64[dst] : sd.v32[dst]);
+  TV *w = (TV *)(sizeof(TV) == 8 ? sd.v64[VWL] : sd.v32[VWL]);
   const TG *G = (const TG *)(sizeof(TG) == 8   ? sd.G64
                              : sizeof(TG) == 4 ? sd.G32
                                                : sd.G16);
   const TC *D = (const TC *)(sizeof(TC) == 8 ? sd.D64 : sd.D32);
-  // the element energies (p, A p) terms are stored with every application;
   // the output streams non-temporally (a batch's E-vectors together are far
   // larger than the caches: 256 solves 6.98 -> 6.85 s)
-  ax_tile<N1, BTile<BS, N1>::EPB, TV, TG, TV, TC, true, true, false, true, true>(
-      threadIdx.x, e0, sd.E, D, G, u, w, &sd.box, smem, nullptr, sd.edot);
+  ax_tile<N1, BTile<BS, N1>::EPB, TV, TG, TV, TC, true, true, false, true, DIR != 0, false, DIR>(
+      threadIdx.x, e0, sd.E, D, G, u, w, &sd.box, smem, nullptr, DIR ? sd.edot : nullptr,
+      DIR == 1 || DIR == 2 ? &dir : nullptr);
 }
 
-template <int BS, class TV, class TG, class TC, int... N1s>
+template <int BS, class TV, class TG, class TC, int DIR, int... N1s>
 __global__ void __launch_bounds__(BS)
-    k_bax(const BatchSolve *__restrict__ sds, const CgState *__restrict__ st,
-          const AxItem *__restrict__ items, int nitems, int src, int dst,
-          int skip_done) {
+    k_bax(const BatchSolve *__restrict__ sds, CgState *st,
+          const AxItem *__restrict__ items, int nitems, int src, BaxDir bd) {
   extern __shared__ __align__(16) unsigned char dyn_smem[];
   TC *smem = reinterpret_cast<TC *>(dyn_smem);
   for (int q = blockIdx.x; q < nitems; q += gridDim.x) {
     const AxItem it = items[q];
-    if (skip_done && st[it.solve].done != 0) continue;  // uniform per block
     const BatchSolve &sd = sds[it.solve];
+    DirArgs<TV> dir = {};
+    if constexpr (DIR == 1 || DIR == 2) dir = batch_dir<TV>(sd, st, bd, it.solve);
+    // a finished solve: at most its first tile goes on, to pass the flag to
+    // the r update
+    if (DIR != 0 && st[it.solve].done != 0 && (DIR == 3 || it.elem0 != 0))
+      continue;  // uniform per block
     const int n1 = sd.N1;
     // exactly one of the compiled orders matches the item's order
-    ((n1 == N1s ? bax_one<BS, TV, TG, TC, N1s>(sd, it.elem0, src, dst, smem)
+    ((n1 == N1s ? bax_one<BS, TV, TG, TC, DIR, N1s>(sd, it.elem0, src, dir, smem)
                 : void()),
      ...);
     __syncthreads();  // the next item may use another LDS layout
@@ -155,64 +164,81 @@ template <int BS, class TC, int... N1s> constexpr int max_lds_words() {
   return m;
 }
 
-template <int BS, class TV, class TG, class TC, int... N1s>
-static void launch_bax_set(const BatchSolve *sds, const CgState *st,
-                           const AxItem *items, int nitems, int grid, int src,
-                           int dst, int skip_done, hipStream_t s) {
+template <int BS, class TV, class TG, class TC, int DIR, int... N1s>
+static void launch_bax_set(const BatchSolve *sds, CgState *st, const AxItem *items,
+                           int nitems, int grid, int src, const BaxDir &bd,
+                           hipStream_t s) {
   const size_t lds = (size_t)max_lds_words<BS, TC, N1s...>() * sizeof(TC);
-  hipLaunchKernelGGL((k_bax<BS, TV, TG, TC, N1s...>), dim3(grid), dim3(BS), lds,
-                     s, sds, st, items, nitems, src, dst, skip_done);
+  hipLaunchKernelGGL((k_bax<BS, TV, TG, TC, DIR, N1s...>), dim3(grid), dim3(BS), lds,
+                     s, sds, st, items, nitems, src, bd);
 }
 
-template <int BS, class TV, class TG, class TC>
-static void launch_bax_bs(int nset, const BatchSolve *sds, const CgState *st,
+template <int BS, class TV, class TG, class TC, int DIR>
+static void launch_bax_bs(int nset, const BatchSolve *sds, CgState *st,
                           const AxItem *items, int nitems, int grid, int src,
-                          int dst, int skip_done, hipStream_t s) {
+                          const BaxDir &bd, hipStream_t s) {
   // a thread owns one (i, j) column: a workgroup must hold every column of
   // the largest order of the set
   if (BS < bax_min_block(nset))
     fail(SEM_ERR_ARG, "batched operator: block size below n1^2 of an order");
   // order sets compiled: one order (n1 = 2..9) or the mixed set {4, 6, 8}
   switch (nset) {
-    case 2: launch_bax_set<BS, TV, TG, TC, 2>(sds, st, items, nitems, grid, src, dst, skip_done, s); break;
-    case 3: launch_bax_set<BS, TV, TG, TC, 3>(sds, st, items, nitems, grid, src, dst, skip_done, s); break;
-    case 4: launch_bax_set<BS, TV, TG, TC, 4>(sds, st, items, nitems, grid, src, dst, skip_done, s); break;
-    case 5: launch_bax_set<BS, TV, TG, TC, 5>(sds, st, items, nitems, grid, src, dst, skip_done, s); break;
-    case 6: launch_bax_set<BS, TV, TG, TC, 6>(sds, st, items, nitems, grid, src, dst, skip_done, s); break;
-    case 7: launch_bax_set<BS, TV, TG, TC, 7>(sds, st, items, nitems, grid, src, dst, skip_done, s); break;
-    case 8: launch_bax_set<BS, TV, TG, TC, 8>(sds, st, items, nitems, grid, src, dst, skip_done, s); break;
-    case 9: launch_bax_set<BS, TV, TG, TC, 9>(sds, st, items, nitems, grid, src, dst, skip_done, s); break;
-    case AX_SET_468: launch_bax_set<BS, TV, TG, TC, 4, 6, 8>(sds, st, items, nitems, grid, src, dst, skip_done, s); break;
+#define SEM_BAX(...)                                                                      \
+  launch_bax_set<BS, TV, TG, TC, DIR, __VA_ARGS__>(sds, st, items, nitems, grid, src, bd, s); \
+  break
+    case 2: SEM_BAX(2);
+    case 3: SEM_BAX(3);
+    case 4: SEM_BAX(4);
+    case 5: SEM_BAX(5);
+    case 6: SEM_BAX(6);
+    case 7: SEM_BAX(7);
+    case 8: SEM_BAX(8);
+    case 9: SEM_BAX(9);
+    case AX_SET_468: SEM_BAX(4, 6, 8);
+#undef SEM_BAX
     default: fail(SEM_ERR_ARG, "batched operator: unsupported set of orders");
   }
 }
 
-template <class TV, class TG, class TC>
-static void launch_bax_t(int bs, int nset, const BatchSolve *sds,
-                         const CgState *st, const AxItem *items, int nitems,
-                         int grid, int src, int dst, int skip_done,
-                         hipStream_t s) {
+template <class TV, class TG, class TC, int DIR>
+static void launch_bax_t(int bs, int nset, const BatchSolve *sds, CgState *st,
+                         const AxItem *items, int nitems, int grid, int src,
+                         const BaxDir &bd, hipStream_t s) {
   switch (bs) {
-    case 64: launch_bax_bs<64, TV, TG, TC>(nset, sds, st, items, nitems, grid, src, dst, skip_done, s); break;
-    case 128: launch_bax_bs<128, TV, TG, TC>(nset, sds, st, items, nitems, grid, src, dst, skip_done, s); break;
-    case 256: launch_bax_bs<256, TV, TG, TC>(nset, sds, st, items, nitems, grid, src, dst, skip_done, s); break;
+    case 64: launch_bax_bs<64, TV, TG, TC, DIR>(nset, sds, st, items, nitems, grid, src, bd, s); break;
+    case 128: launch_bax_bs<128, TV, TG, TC, DIR>(nset, sds, st, items, nitems, grid, src, bd, s); break;
+    case 256: launch_bax_bs<256, TV, TG, TC, DIR>(nset, sds, st, items, nitems, grid, src, bd, s); break;
     default: fail(SEM_ERR_ARG, "batched operator: block size must be 64, 128 or 256");
   }
 }
 
-void launch_bax(int prec, int bs, int nset, const BatchSolve *sds,
-                const CgState *st, const AxItem *items, int nitems, int grid,
-                int src, int dst, int skip_done, hipStream_t s) {
-  if (nitems <= 0) return;
+template <int DIR>
+static void launch_bax_d(int prec, int bs, int nset, const BatchSolve *sds, CgState *st,
+                         const AxItem *items, int nitems, int grid, int src,
+                         const BaxDir &bd, hipStream_t s) {
   if (prec == SEM_FP64)
-    launch_bax_t<double, double, double>(bs, nset, sds, st, items, nitems, grid,
-                                         src, dst, skip_done, s);
+    launch_bax_t<double, double, double, DIR>(bs, nset, sds, st, items, nitems, grid, src,
+                                              bd, s);
   else if (prec == SEM_FP32)
-    launch_bax_t<float, float, float>(bs, nset, sds, st, items, nitems, grid, src,
-                                      dst, skip_done, s);
+    launch_bax_t<float, float, float, DIR>(bs, nset, sds, st, items, nitems, grid, src, bd,
+                                           s);
   else
-    launch_bax_t<float, uint16_t, float>(bs, nset, sds, st, items, nitems, grid,
-                                         src, dst, skip_done, s);
+    launch_bax_t<float, uint16_t, float, DIR>(bs, nset, sds, st, items, nitems, grid, src,
+                                              bd, s);
+}
+
+void launch_bax(int prec, int bs, int nset, const BatchSolve *sds, CgState *st,
+                const AxItem *items, int nitems, int grid, int src, const BaxDir &bd,
+                hipStream_t s) {
+  if (nitems <= 0) return;
+  if (bd.mode == 0)
+    launch_bax_d<0>(prec, bs, nset, sds, st, items, nitems, grid, src, bd, s);
+  else if (bd.mode == 1)
+    launch_bax_d<1>(prec, bs, nset, sds, st, items, nitems, grid, src, bd, s);
+  else if (bd.mode == 2)
+    launch_bax_d<2>(prec, bs, nset, sds, st, items, nitems, grid, src, bd, s);
+  else
+    launch_bax_d<3>(prec, bs, nset, sds, st, items, nitems, grid, src, bd, s);
   SEM_HIP(hipGetLastError());
 }
 

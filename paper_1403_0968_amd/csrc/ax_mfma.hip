@@ -548,31 +548,93 @@ void launch_ax_mfma(int N, bool split, int64_t E, const uint16_t *Dhi,
 // operator's spread of eigenvalues, and the refinement's contraction grew
 // with the mesh (0.36 per step at 32^3 elements, N = 7).
 // ---------------------------------------------------------------------------
-// want_edot: also store every element's energy p_e^T w_e in FP64 (the terms
-// of (p, A p) for the solvers), each lane's column of the FP32 input p times
-// the stored w in ascending k, then the lanes by a fixed butterfly
-// One element of the solvers' operator (gathered FP32 input p, split into
-// two BF16 terms; FP32 output; with edot non-null the element energy).
-// Every wave of the workgroup calls it (act = false: no loads or stores),
-// since the element routine synchronises the workgroup.
+// The solvers apply this operator to the search direction only: its gathered
+// input z (mode 3), or p' = z + beta p (cg_dir.h), which is then stored.
+struct DirMfma {
+  gp<const float> z, p;
+  gp<float> pnew;  // null in mode 3
+  float beta;
+  bool first;      // the direction is z
+};
+
+// beta and first of the direction; true when the solve has ended
+__device__ inline bool dir_mfma(CgState *st, int mode, const double *part, int stride, int beg,
+                                int end, bool writer, DirMfma &dir) {
+  const DirScalars s = dir_scalars(st);
+  dir.beta = 0.f;
+  dir.first = true;
+  if (mode == 3) return s.done != 0;
+  DirStep ds;
+  if (mode == 2) {
+    DirParts<true> parts;
+    parts.load(part, stride, beg, end);
+    ds = dir_step<true>(st, s, parts, writer);
+  } else {
+    ds = dir_step<false>(st, s, DirParts<false>(), writer);
+  }
+  dir.beta = (float)ds.beta;
+  dir.first = ds.first;
+  return ds.stop;
+}
+
+// the NT nodes of one lane, node(t, i, j, k) giving each one's place in the
+// element (false: no node): p' into v (0 where there is none), stored by the
+// element that owns the node
+template <int NT, class F>
+__device__ inline void gather_dir(const Box &box, const DirMfma &d, bool act, int64_t e,
+                                  F node, float (&v)[NT]) {
+  ElemXYZ c3 = {0u, 0u, 0u};
+  if (act) c3 = box_elem(box, (uint32_t)e);
+  int64_t g[NT];
+  float po[NT];
+  bool own[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    uint32_t i, j, k;
+    const bool in = node(t, i, j, k) && act;
+    const uint32_t gx = wrap_coord(c3.x * (uint32_t)box.N + i, box.Gx);
+    const uint32_t gy = wrap_coord(c3.y * (uint32_t)box.N + j, box.Gy);
+    const uint32_t gz = wrap_coord(c3.z * (uint32_t)box.N + k, box.Gz);
+    g[t] = (int64_t)gx + (int64_t)box.Gx * ((int64_t)gy + (int64_t)box.Gy * gz);
+    v[t] = in ? d.z[g[t]] : 0.f;
+    po[t] = in && d.pnew != nullptr ? d.p[g[t]] : 0.f;
+    own[t] = in && d.pnew != nullptr && owns_coord(i, c3.x, gx) && owns_coord(j, c3.y, gy) &&
+             owns_coord(k, c3.z, gz);
+  }
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+    if (!d.first) v[t] = v[t] + d.beta * po[t];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+    if (own[t]) d.pnew[g[t]] = v[t];
+}
+
+// One element of the solvers' operator (gathered FP32 direction, split into
+// two BF16 terms; FP32 output), and the element energy p'_e^T w_e in FP64:
+// each lane's column of p' times the stored w in ascending k, then the lanes
+// by a fixed butterfly.  Every wave of the workgroup calls it (act = false:
+// no loads or stores).
 template <int N1, bool SPLIT>
 __device__ inline void solve_elem_mfma(int l, MfmaLdsSplit &L, int64_t e, bool act,
-                                       const Box &box, gp<const float> u, gp<float> w,
+                                       const Box &box, const DirMfma &dir, gp<float> w,
                                        const uint16_t *G, gp<const uint16_t> H,
                                        m16x4 fh, m16x4 fl, m16x4 bh, m16x4 bl,
                                        gp<double> edot) {
   constexpr int NP = N1 * N1, N3 = NP * N1;
   uint16_t gq[6][8];
   load_factors<N1>(l, act, e, G, gq);
-  ElemXYZ c3 = {0u, 0u, 0u};
-  if (act) c3 = box_elem(box, (uint32_t)e);
-  float pv[8];  // the lane's column (i, j) = (l % 8, l / 8) of p, k = t
+  float pv[8];  // the lane's column (i, j) = (l % 8, l / 8) of p', k = t
+  gather_dir(
+      box, dir, act, e,
+      [&](int t, uint32_t &i, uint32_t &j, uint32_t &k) {
+        i = l & 7, j = l >> 3, k = t;
+        return i < N1 && j < N1 && k < N1;
+      },
+      pv);
 #pragma unroll
   for (int t = 0; t < 8; ++t) {
-    const int p = l + 64 * t, i = p & 7, j = (p >> 3) & 7, k = p >> 6;
-    const bool in = act && i < N1 && j < N1 && k < N1;
-    const float v = in ? u[box_node(box, c3, i, j, k)] : 0.f;
-    pv[t] = v;
+    const int p = l + 64 * t;
+    const float v = pv[t];
     const uint16_t hi = f32_to_bf16(v);
     L.u[p] = hi;
     L.ul[p] = f32_to_bf16(v - bf16_to_f32(hi));
@@ -591,33 +653,42 @@ __device__ inline void solve_elem_mfma(int l, MfmaLdsSplit &L, int64_t e, bool a
   if (act) {
     for (int p = l; p < N3; p += 64) w[e * N3 + p] = wval(p % N1, (p / N1) % N1, p / NP);
   }
-  if (edot != nullptr) {  // uniform
-    const int i = l & 7, j = l >> 3;
-    double cd = 0.0;
-    if (i < N1 && j < N1) {
+  const int i = l & 7, j = l >> 3;
+  double cd = 0.0;
+  if (i < N1 && j < N1) {
 #pragma unroll
-      for (int t = 0; t < N1; ++t) cd += (double)pv[t] * (double)wval(i, j, t);
-    }
-    cd = wave_sum(cd);
-    if (act && l == 0) edot[e] = cd;
+    for (int t = 0; t < N1; ++t) cd += (double)pv[t] * (double)wval(i, j, t);
   }
+  cd = wave_sum(cd);
+  if (act && l == 0) edot[e] = cd;
 }
 
-// want_edot: also store every element's energy p_e^T w_e in FP64 (the terms
-// of (p, A p) for the solvers), each lane's column of the FP32 input p times
-// the stored w in ascending k, then the lanes by a fixed butterfly
+// the direction of a batch's item; true when the item has nothing to do (the
+// solve has ended; its first tile has passed that on)
+__device__ inline bool batch_dir_mfma(const BatchSolve &sd, CgState *st, const BaxDir &bd,
+                                      const AxItem &it, DirMfma &dir) {
+  const bool first_tile = it.elem0 == 0;
+  if (st[it.solve].done != 0 && !first_tile) return true;  // (mode 3: dir_mfma)
+  const bool writer = first_tile && threadIdx.x == 0;
+  const int beg = bd.vbeg[it.solve], end = bd.vbeg[it.solve + 1];
+  dir.z = (gp<const float>)sd.v32[bd.mode == 3 ? VP : VZ];
+  dir.p = (gp<const float>)sd.v32[bd.par ? VW : VP];
+  dir.pnew = bd.mode == 3 ? (gp<float>)nullptr : (gp<float>)sd.v32[bd.par ? VP : VW];
+  return dir_mfma(st + it.solve, bd.mode, bd.part, bd.stride, beg, end, writer, dir);
+}
+
 template <int N1, bool SPLIT>
 __global__ void __launch_bounds__(64 * MW)
-    k_bax_mfma(const BatchSolve *__restrict__ sds, const CgState *__restrict__ st,
-               const AxItem *__restrict__ items, int nitems, int epb, int src,
-               int dst, int skip_done, int want_edot) {
+    k_bax_mfma(const BatchSolve *__restrict__ sds, CgState *st,
+               const AxItem *__restrict__ items, int nitems, int epb, BaxDir bd) {
   __shared__ MfmaLdsSplit lds[MW];
   const int wv = threadIdx.x >> 6, l = threadIdx.x & 63;
   MfmaLdsSplit &L = lds[wv];
   for (int q = blockIdx.x; q < nitems; q += gridDim.x) {
     const AxItem it = items[q];
-    if (skip_done && st[it.solve].done != 0) continue;  // uniform per block
     const BatchSolve &sd = sds[it.solve];
+    DirMfma dir;
+    if (batch_dir_mfma(sd, st, bd, it, dir)) continue;  // uniform per block
     m16x4 fh, fl, bh, bl;
     d_operands<N1>(l, (const uint16_t *)sd.D16hi, (const uint16_t *)sd.D16lo, fh,
                    fl, bh, bl);
@@ -625,9 +696,9 @@ __global__ void __launch_bounds__(64 * MW)
       const int64_t e = it.elem0 + e0 + wv;
       // global pointers (their address space is not known from the descriptor)
       solve_elem_mfma<N1, SPLIT>(
-          l, L, e, e0 + wv < epb && e < sd.E, sd.box, (gp<const float>)sd.v32[src],
-          (gp<float>)sd.v32[dst], (const uint16_t *)sd.G16, (gp<const uint16_t>)sd.H16,
-          fh, fl, bh, bl, want_edot ? (gp<double>)sd.edot : nullptr);
+          l, L, e, e0 + wv < epb && e < sd.E, sd.box, dir, (gp<float>)sd.v32[VWL],
+          (const uint16_t *)sd.G16, (gp<const uint16_t>)sd.H16, fh, fl, bh, bl,
+          (gp<double>)sd.edot);
       wave_lds_sync();  // L is reused by the next element
     }
   }
@@ -640,45 +711,51 @@ template <int N1, bool SPLIT>
 __global__ void __launch_bounds__(64 * MW)
     k_ax_mfma_solve(int64_t E, const uint16_t *__restrict__ Dhi,
                     const uint16_t *__restrict__ Dlo, const uint16_t *__restrict__ G,
-                    const uint16_t *__restrict__ H, const float *__restrict__ u,
-                    float *__restrict__ w, Box box, const int32_t *__restrict__ stop,
+                    const uint16_t *__restrict__ H, const float *__restrict__ z,
+                    float *__restrict__ w, Box box, DirArgs<float> da, int mode,
                     double *__restrict__ edot) {
   __shared__ MfmaLdsSplit lds[MW];
   const int wv = threadIdx.x >> 6, l = threadIdx.x & 63;
-  if (stop != nullptr && *stop != 0) return;  // uniform: the solve is done
+  DirMfma dir;
+  dir.z = (gp<const float>)z;
+  dir.p = (gp<const float>)da.p;
+  dir.pnew = (gp<float>)da.pnew;
+  if (dir_mfma(da.st, mode, da.part, da.stride, da.beg, da.end,
+               blockIdx.x == 0 && threadIdx.x == 0, dir))
+    return;  // uniform: the solve has ended
   m16x4 fh, fl, bh, bl;
   d_operands<N1>(l, Dhi, Dlo, fh, fl, bh, bl);
   const int64_t e = (int64_t)blockIdx.x * MW + wv;
-  solve_elem_mfma<N1, SPLIT>(l, lds[wv], e, e < E, box, (gp<const float>)u, (gp<float>)w,
-                             G, (gp<const uint16_t>)H, fh, fl, bh, bl,
-                             (gp<double>)edot);
+  solve_elem_mfma<N1, SPLIT>(l, lds[wv], e, e < E, box, dir, (gp<float>)w, G,
+                             (gp<const uint16_t>)H, fh, fl, bh, bl, (gp<double>)edot);
 }
 
 // one element of the solvers' operator at n1 = 9 (as solve_elem_mfma)
 template <bool SPLIT>
 __device__ inline void solve_elem_mfma9(int l, MfmaLds9 &L, int64_t e, bool act,
-                                        const Box &box, gp<const float> u, gp<float> w,
+                                        const Box &box, const DirMfma &dir, gp<float> w,
                                         const uint16_t *G, gp<const uint16_t> H,
                                         m16x4 fh, m16x4 fl, m16x4 bh, m16x4 bl,
                                         gp<double> edot) {
   uint16_t gq[2][6][9];
   load_factors9(l, act, e, G, gq);
-  ElemXYZ c3 = {0u, 0u, 0u};
-  if (act) c3 = box_elem(box, (uint32_t)e);
   constexpr int T9 = (E9 + 63) / 64;
-  float pv[T9];  // p at the lane's nodes p = l + 64 t
+  float pv[T9];  // p' at the lane's nodes p = l + 64 t
+  gather_dir(
+      box, dir, act, e,
+      [&](int t, uint32_t &i, uint32_t &j, uint32_t &k) {
+        const uint32_t p = l + 64 * t;
+        i = p % 9, j = (p / 9) % 9, k = p / 81;
+        return p < E9;
+      },
+      pv);
 #pragma unroll
   for (int t = 0; t < T9; ++t) {
     const int p = l + 64 * t;
     if (p < E9) {
-      const int i = p % 9, j = (p / 9) % 9, k = p / 81;
-      const float v = act ? u[box_node(box, c3, i, j, k)] : 0.f;
-      pv[t] = v;
-      const uint16_t hi = f32_to_bf16(v);
+      const uint16_t hi = f32_to_bf16(pv[t]);
       L.u[p] = hi;
-      L.ul[p] = f32_to_bf16(v - bf16_to_f32(hi));
-    } else {
-      pv[t] = 0.f;
+      L.ul[p] = f32_to_bf16(pv[t] - bf16_to_f32(hi));
     }
   }
   wave_lds_sync();
@@ -692,39 +769,38 @@ __device__ inline void solve_elem_mfma9(int l, MfmaLds9 &L, int64_t e, bool act,
   if (act) {
     for (int p = l; p < E9; p += 64) w[e * E9 + p] = wval(p);
   }
-  if (edot != nullptr) {  // uniform; each lane's nodes in ascending t, then the lanes
-    double cd = 0.0;
+  // each lane's nodes in ascending t, then the lanes
+  double cd = 0.0;
 #pragma unroll
-    for (int t = 0; t < T9; ++t)
-      if (l + 64 * t < E9) cd += (double)pv[t] * (double)wval(l + 64 * t);
-    cd = wave_sum(cd);
-    if (act && l == 0) edot[e] = cd;
-  }
+  for (int t = 0; t < T9; ++t)
+    if (l + 64 * t < E9) cd += (double)pv[t] * (double)wval(l + 64 * t);
+  cd = wave_sum(cd);
+  if (act && l == 0) edot[e] = cd;
 }
 
 // the batched solver operator at n1 = 9: as k_bax_mfma, MW9 elements per
 // workgroup pass
 template <bool SPLIT>
 __global__ void __launch_bounds__(64 * MW9)
-    k_bax_mfma9(const BatchSolve *__restrict__ sds, const CgState *__restrict__ st,
-                const AxItem *__restrict__ items, int nitems, int epb, int src,
-                int dst, int skip_done, int want_edot) {
+    k_bax_mfma9(const BatchSolve *__restrict__ sds, CgState *st,
+                const AxItem *__restrict__ items, int nitems, int epb, BaxDir bd) {
   __shared__ MfmaLds9 lds[MW9];
   const int wv = threadIdx.x >> 6, l = threadIdx.x & 63;
   MfmaLds9 &L = lds[wv];
   for (int q = blockIdx.x; q < nitems; q += gridDim.x) {
     const AxItem it = items[q];
-    if (skip_done && st[it.solve].done != 0) continue;  // uniform per block
     const BatchSolve &sd = sds[it.solve];
+    DirMfma dir;
+    if (batch_dir_mfma(sd, st, bd, it, dir)) continue;  // uniform per block
     m16x4 fh, fl, bh, bl;
     d_operands9(l, (const uint16_t *)sd.D16hi, (const uint16_t *)sd.D16lo, fh, fl,
                 bh, bl);
     for (int e0 = 0; e0 < epb; e0 += MW9) {  // uniform per block
       const int64_t e = it.elem0 + e0 + wv;
       solve_elem_mfma9<SPLIT>(
-          l, L, e, e0 + wv < epb && e < sd.E, sd.box, (gp<const float>)sd.v32[src],
-          (gp<float>)sd.v32[dst], (const uint16_t *)sd.G16, (gp<const uint16_t>)sd.H16,
-          fh, fl, bh, bl, want_edot ? (gp<double>)sd.edot : nullptr);
+          l, L, e, e0 + wv < epb && e < sd.E, sd.box, dir, (gp<float>)sd.v32[VWL],
+          (const uint16_t *)sd.G16, (gp<const uint16_t>)sd.H16, fh, fl, bh, bl,
+          (gp<double>)sd.edot);
       wave_lds_sync();  // L is reused by the next element
     }
   }
@@ -735,46 +811,47 @@ template <bool SPLIT>
 __global__ void __launch_bounds__(64 * MW9)
     k_ax_mfma_solve9(int64_t E, const uint16_t *__restrict__ Dhi,
                      const uint16_t *__restrict__ Dlo, const uint16_t *__restrict__ G,
-                     const uint16_t *__restrict__ H, const float *__restrict__ u,
-                     float *__restrict__ w, Box box, const int32_t *__restrict__ stop,
+                     const uint16_t *__restrict__ H, const float *__restrict__ z,
+                     float *__restrict__ w, Box box, DirArgs<float> da, int mode,
                      double *__restrict__ edot) {
   __shared__ MfmaLds9 lds[MW9];
   const int wv = threadIdx.x >> 6, l = threadIdx.x & 63;
-  if (stop != nullptr && *stop != 0) return;  // uniform: the solve is done
+  DirMfma dir;
+  dir.z = (gp<const float>)z;
+  dir.p = (gp<const float>)da.p;
+  dir.pnew = (gp<float>)da.pnew;
+  if (dir_mfma(da.st, mode, da.part, da.stride, da.beg, da.end,
+               blockIdx.x == 0 && threadIdx.x == 0, dir))
+    return;  // uniform: the solve has ended
   m16x4 fh, fl, bh, bl;
   d_operands9(l, Dhi, Dlo, fh, fl, bh, bl);
   const int64_t e = (int64_t)blockIdx.x * MW9 + wv;
-  solve_elem_mfma9<SPLIT>(l, lds[wv], e, e < E, box, (gp<const float>)u, (gp<float>)w, G,
+  solve_elem_mfma9<SPLIT>(l, lds[wv], e, e < E, box, dir, (gp<float>)w, G,
                           (gp<const uint16_t>)H, fh, fl, bh, bl, (gp<double>)edot);
 }
 
-void launch_ax_mfma_solve(int N, bool split, int64_t E, const uint16_t *Dhi,
-                          const uint16_t *Dlo, const uint16_t *G, const uint16_t *H,
-                          const float *u, float *w, const Box &box, const int32_t *stop,
-                          double *edot, hipStream_t s) {
-  if (E <= 0) return;
-  const int n1 = N + 1;
-  if (n1 == 9) {
-    const dim3 g((unsigned)((E + MW9 - 1) / MW9)), b(64 * MW9);
-    if (split)
-      hipLaunchKernelGGL((k_ax_mfma_solve9<true>), g, b, 0, s, E, Dhi, Dlo, G, H, u, w,
-                         box, stop, edot);
-    else
-      hipLaunchKernelGGL((k_ax_mfma_solve9<false>), g, b, 0, s, E, Dhi, Dlo, G, H, u, w,
-                         box, stop, edot);
-    SEM_HIP(hipGetLastError());
-    return;
-  }
-  const dim3 g((unsigned)((E + MW - 1) / MW)), b(64 * MW);
+void launch_ax_mfma_solve(const SolveAx &a, hipStream_t s) {
+  if (a.E <= 0) return;
+  if (a.mode == 0) fail(SEM_ERR_ARG, "solve: the matrix-core operator runs inside CG only");
+  const int n1 = a.N + 1;
+  const bool split = a.prec == SEM_BF16_MFMA;
+  const DirArgs<float> da = {(const float *)a.p, a.mode == 3 ? nullptr : (float *)a.pnew,
+                             a.st,               a.part,
+                             a.nparts,           0,
+                             a.nparts};
+  auto go = [&](auto kernel, int waves) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((a.E + waves - 1) / waves)), dim3(64 * waves),
+                       0, s, a.E, (const uint16_t *)a.D, (const uint16_t *)a.Dlo,
+                       (const uint16_t *)a.G, (const uint16_t *)a.H, (const float *)a.u,
+                       (float *)a.w, a.box, da, a.mode, a.edot);
+  };
   switch (n1) {
-#define SEM_AXMS(NN)                                                                  \
-  case NN:                                                                            \
-    if (split)                                                                        \
-      hipLaunchKernelGGL((k_ax_mfma_solve<NN, true>), g, b, 0, s, E, Dhi, Dlo, G, H,  \
-                         u, w, box, stop, edot);                                      \
-    else                                                                              \
-      hipLaunchKernelGGL((k_ax_mfma_solve<NN, false>), g, b, 0, s, E, Dhi, Dlo, G, H, \
-                         u, w, box, stop, edot);                                      \
+#define SEM_AXMS(NN)                          \
+  case NN:                                    \
+    if (split)                                \
+      go(k_ax_mfma_solve<NN, true>, MW);      \
+    else                                      \
+      go(k_ax_mfma_solve<NN, false>, MW);     \
     break;
     SEM_AXMS(2)
     SEM_AXMS(3)
@@ -784,27 +861,34 @@ void launch_ax_mfma_solve(int N, bool split, int64_t E, const uint16_t *Dhi,
     SEM_AXMS(7)
     SEM_AXMS(8)
 #undef SEM_AXMS
+    case 9:
+      if (split)
+        go(k_ax_mfma_solve9<true>, MW9);
+      else
+        go(k_ax_mfma_solve9<false>, MW9);
+      break;
     default:
       fail(SEM_ERR_ARG, "solve: the matrix-core operator needs N in 1..8");
   }
   SEM_HIP(hipGetLastError());
 }
 
-void launch_bax_mfma(int n1, bool split, const BatchSolve *sds, const CgState *st,
-                     const AxItem *items, int nitems, int epb, int grid, int src,
-                     int dst, int skip_done, bool edot, hipStream_t s) {
-  const int want_edot = edot ? 1 : 0;
+void launch_bax_mfma(int n1, bool split, const BatchSolve *sds, CgState *st,
+                     const AxItem *items, int nitems, int epb, int grid, const BaxDir &bd,
+                     hipStream_t s) {
   if (nitems <= 0) return;
-  const dim3 g((unsigned)grid), b(64 * MW);
+  if (bd.mode == 0) fail(SEM_ERR_ARG, "solve: the matrix-core operator runs inside CG only");
+  auto go = [&](auto kernel, int waves) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * waves), 0, s, sds, st, items,
+                       nitems, epb, bd);
+  };
   switch (n1) {
-#define SEM_BAXM(NN)                                                            \
-  case NN:                                                                      \
-    if (split)                                                                  \
-      hipLaunchKernelGGL((k_bax_mfma<NN, true>), g, b, 0, s, sds, st, items,    \
-                         nitems, epb, src, dst, skip_done, want_edot);          \
-    else                                                                        \
-      hipLaunchKernelGGL((k_bax_mfma<NN, false>), g, b, 0, s, sds, st, items,   \
-                         nitems, epb, src, dst, skip_done, want_edot);          \
+#define SEM_BAXM(NN)                     \
+  case NN:                               \
+    if (split)                           \
+      go(k_bax_mfma<NN, true>, MW);      \
+    else                                 \
+      go(k_bax_mfma<NN, false>, MW);     \
     break;
     SEM_BAXM(2)
     SEM_BAXM(3)
@@ -814,16 +898,12 @@ void launch_bax_mfma(int n1, bool split, const BatchSolve *sds, const CgState *s
     SEM_BAXM(7)
     SEM_BAXM(8)
 #undef SEM_BAXM
-    case 9: {
-      const dim3 b9(64 * MW9);
+    case 9:
       if (split)
-        hipLaunchKernelGGL((k_bax_mfma9<true>), g, b9, 0, s, sds, st, items, nitems,
-                           epb, src, dst, skip_done, want_edot);
+        go(k_bax_mfma9<true>, MW9);
       else
-        hipLaunchKernelGGL((k_bax_mfma9<false>), g, b9, 0, s, sds, st, items, nitems,
-                           epb, src, dst, skip_done, want_edot);
+        go(k_bax_mfma9<false>, MW9);
       break;
-    }
     default:
       fail(SEM_ERR_ARG, "batched operator: the matrix-core operator needs N in 1..8");
   }

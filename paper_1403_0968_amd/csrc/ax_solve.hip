@@ -32,84 +32,81 @@ __device__ inline int64_t xcd_run_block(unsigned b, unsigned nb) {
   return (int64_t)x * q + (x < r ? x : r) + k;
 }
 
-template <int N1, class TV, class TG, class TC, bool MASS, bool EDOT, bool NTW>
-__global__ void __launch_bounds__((OpShape<N1, sizeof(TC)>::THREADS))
+// threads: whole waves where the direction's scalars are formed by waves
+template <int N1, class TC, int DIR> constexpr int solve_threads() {
+  constexpr int T = OpShape<N1, sizeof(TC)>::THREADS;
+  return DIR != 0 ? (T + 63) / 64 * 64 : T;
+}
+
+template <int N1, class TV, class TG, class TC, bool MASS, bool NTW, int DIR>
+__global__ void __launch_bounds__((solve_threads<N1, TC, DIR>()))
     k_ax_solve(int64_t E, const TC *__restrict__ D, const TG *__restrict__ G,
                const TV *__restrict__ u, TV *__restrict__ w, Box box,
-               const int32_t *__restrict__ stop, const TG *__restrict__ H,
-               double *__restrict__ edot) {
+               const TG *__restrict__ H, double *__restrict__ edot, DirArgs<TV> dir) {
   using S = OpShape<N1, sizeof(TC)>;
   __shared__ __align__(16) TC smem[lds_words<N1, TC>(S::EPB)];
-  // the done flag of the solve is checked inside, after the loads are issued
-  ax_tile<N1, S::EPB, TV, TG, TV, TC, true, NTW, MASS, S::NTG, EDOT, S::PRED>(
+  ax_tile<N1, S::EPB, TV, TG, TV, TC, true, NTW, MASS, S::NTG, DIR != 0, S::PRED, DIR>(
       threadIdx.x,
       (sizeof(TV) == 4 ? xcd_run_block(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x) *
           S::EPB,
-      E, D, G, u, w, &box, smem, H, edot, stop);
+      E, D, G, u, w, &box, smem, H, edot, DIR != 0 ? &dir : nullptr);
 }
 
-template <int N1, class TV, class TG, class TC, bool MASS, bool NTW>
-static void launch_solve_w(int64_t E, const void *D, const void *G,
-                           const void *H, const void *u, void *w, const Box &box,
-                           const int32_t *stop, double *edot, hipStream_t s) {
+template <int N1, class TV, class TG, class TC, bool MASS, bool NTW, int DIR>
+static void launch_solve_d(const SolveAx &a, hipStream_t s) {
   using S = OpShape<N1, sizeof(TC)>;
-  const int64_t blocks = (E + S::EPB - 1) / S::EPB;
+  const int64_t blocks = (a.E + S::EPB - 1) / S::EPB;
   if (blocks == 0) return;
-  const dim3 grid((unsigned)blocks), block(S::THREADS);
-  if (edot != nullptr)
-    hipLaunchKernelGGL((k_ax_solve<N1, TV, TG, TC, MASS, true, NTW>), grid, block, 0, s,
-                       E, (const TC *)D, (const TG *)G, (const TV *)u, (TV *)w,
-                       box, stop, (const TG *)H, edot);
-  else
-    hipLaunchKernelGGL((k_ax_solve<N1, TV, TG, TC, MASS, false, NTW>), grid, block, 0,
-                       s, E, (const TC *)D, (const TG *)G, (const TV *)u, (TV *)w,
-                       box, stop, (const TG *)H, edot);
+  const DirArgs<TV> dir = {(const TV *)a.p, (TV *)a.pnew, a.st, a.part, a.nparts, 0, a.nparts};
+  hipLaunchKernelGGL((k_ax_solve<N1, TV, TG, TC, MASS, NTW, DIR>), dim3((unsigned)blocks),
+                     dim3(solve_threads<N1, TC, DIR>()), 0, s, a.E, (const TC *)a.D,
+                     (const TG *)a.G, (const TV *)a.u, (TV *)a.w, a.box, (const TG *)a.H,
+                     a.edot, dir);
 }
 
 template <int N1, class TV, class TG, class TC, bool MASS>
-static void launch_solve_m(int64_t E, const void *D, const void *G,
-                           const void *H, const void *u, void *w, const Box &box,
-                           const int32_t *stop, double *edot, bool nt, hipStream_t s) {
-  if (nt)
-    launch_solve_w<N1, TV, TG, TC, MASS, true>(E, D, G, H, u, w, box, stop, edot, s);
+static void launch_solve_m(const SolveAx &a, hipStream_t s) {
+  // the direction is formed in the operator only where the vectors do not
+  // stream, and in a pass of its own where they do
+  if (a.mode == 2)
+    launch_solve_d<N1, TV, TG, TC, MASS, false, 2>(a, s);
+  else if (a.mode == 1)
+    launch_solve_d<N1, TV, TG, TC, MASS, false, 1>(a, s);
+  else if (a.mode == 3)
+    launch_solve_d<N1, TV, TG, TC, MASS, true, 3>(a, s);
+  else if (a.nt)
+    launch_solve_d<N1, TV, TG, TC, MASS, true, 0>(a, s);
   else
-    launch_solve_w<N1, TV, TG, TC, MASS, false>(E, D, G, H, u, w, box, stop, edot, s);
+    launch_solve_d<N1, TV, TG, TC, MASS, false, 0>(a, s);
 }
 
 template <int N1, class TV, class TG, class TC>
-static void launch_solve_t(int64_t E, const void *D, const void *G,
-                           const void *H, const void *u, void *w, const Box &box,
-                           const int32_t *stop, double *edot, bool nt, hipStream_t s) {
-  if (H != nullptr)
-    launch_solve_m<N1, TV, TG, TC, true>(E, D, G, H, u, w, box, stop, edot, nt, s);
+static void launch_solve_t(const SolveAx &a, hipStream_t s) {
+  if (a.H != nullptr)
+    launch_solve_m<N1, TV, TG, TC, true>(a, s);
   else
-    launch_solve_m<N1, TV, TG, TC, false>(E, D, G, H, u, w, box, stop, edot, nt, s);
+    launch_solve_m<N1, TV, TG, TC, false>(a, s);
 }
 
-template <int N1>
-static void launch_solve_n(int prec, int64_t E, const void *D, const void *G,
-                           const void *H, const void *u, void *w, const Box &box,
-                           const int32_t *stop, double *edot, bool nt, hipStream_t s) {
-  if (prec == SEM_FP64)
-    launch_solve_t<N1, double, double, double>(E, D, G, H, u, w, box, stop, edot, nt, s);
-  else if (prec == SEM_FP32)
-    launch_solve_t<N1, float, float, float>(E, D, G, H, u, w, box, stop, edot, nt, s);
+template <int N1> static void launch_solve_n(const SolveAx &a, hipStream_t s) {
+  if (a.prec == SEM_FP64)
+    launch_solve_t<N1, double, double, double>(a, s);
+  else if (a.prec == SEM_FP32)
+    launch_solve_t<N1, float, float, float>(a, s);
   else
-    launch_solve_t<N1, float, uint16_t, float>(E, D, G, H, u, w, box, stop, edot, nt, s);
+    launch_solve_t<N1, float, uint16_t, float>(a, s);
 }
 
-void launch_ax_solve(int N, int prec, int64_t E, const void *D, const void *G,
-                     const void *H, const void *u, void *w, const Box &box,
-                     const int32_t *stop, double *edot, bool nt, hipStream_t s) {
-  switch (N) {
-    case 1: launch_solve_n<2>(prec, E, D, G, H, u, w, box, stop, edot, nt, s); break;
-    case 2: launch_solve_n<3>(prec, E, D, G, H, u, w, box, stop, edot, nt, s); break;
-    case 3: launch_solve_n<4>(prec, E, D, G, H, u, w, box, stop, edot, nt, s); break;
-    case 4: launch_solve_n<5>(prec, E, D, G, H, u, w, box, stop, edot, nt, s); break;
-    case 5: launch_solve_n<6>(prec, E, D, G, H, u, w, box, stop, edot, nt, s); break;
-    case 6: launch_solve_n<7>(prec, E, D, G, H, u, w, box, stop, edot, nt, s); break;
-    case 7: launch_solve_n<8>(prec, E, D, G, H, u, w, box, stop, edot, nt, s); break;
-    case 8: launch_solve_n<9>(prec, E, D, G, H, u, w, box, stop, edot, nt, s); break;
+void launch_ax_solve(const SolveAx &a, hipStream_t s) {
+  switch (a.N) {
+    case 1: launch_solve_n<2>(a, s); break;
+    case 2: launch_solve_n<3>(a, s); break;
+    case 3: launch_solve_n<4>(a, s); break;
+    case 4: launch_solve_n<5>(a, s); break;
+    case 5: launch_solve_n<6>(a, s); break;
+    case 6: launch_solve_n<7>(a, s); break;
+    case 7: launch_solve_n<8>(a, s); break;
+    case 8: launch_solve_n<9>(a, s); break;
     default: fail(SEM_ERR_ARG, "solve: N must be in 1..8");
   }
   SEM_HIP(hipGetLastError());

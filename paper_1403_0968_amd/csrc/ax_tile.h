@@ -18,6 +18,7 @@
 // contiguous).
 #pragma once
 
+#include "cg_dir.h"
 #include "common.h"
 #include "sem_internal.h"
 
@@ -27,14 +28,6 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 template <class P> __device__ inline auto ld_stream(P p) {
   return __builtin_nontemporal_load(p);
-}
-
-// a double moved across the lanes of a wave by a DPP pattern (both halves)
-template <int CTRL> __device__ inline double dpp_f64(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
 // the value of lane `lane` of a wave
@@ -90,9 +83,14 @@ template <int N1, int BYTES> struct OpShape {
 // i and then the rows over j), so that every tile shape gives the same bits.  Inside the solvers u is the
 // search direction p, which vanishes on Dirichlet nodes, and the sum of the
 // element energies is (p, A p) of the assembled operator.
+// DIR != 0 (one CG iteration): nothing is stored once the solve has ended.
+// DIR 3: u is the search direction.  DIR 1 or 2 (cg_dir.h): u is z, and the
+// operator acts on p' = z + beta p, formed here and stored once per unique
+// node; beta comes from the solve's state (1) or from the partial sums (2).
+// All 64 lanes of every wave must then be launched.
 template <int N1, int EPB, class TU, class TG, class TW, class TC, bool GATHER,
           bool NTW, bool MASS = false, bool NTG = true, bool EDOT = false,
-          bool PRED = false>
+          bool PRED = false, int DIR = 0>
 __device__ __forceinline__ void ax_tile(int t, int64_t e0, int64_t E,
                                         const TC *__restrict__ D_,
                                         const TG *__restrict__ G_,
@@ -102,7 +100,9 @@ __device__ __forceinline__ void ax_tile(int t, int64_t e0, int64_t E,
                                         TC *__restrict__ smem,
                                         const TG *__restrict__ H_ = nullptr,
                                         double *__restrict__ edot_ = nullptr,
-                                        const int32_t *__restrict__ stop = nullptr) {
+                                        const DirArgs<TU> *dir = nullptr) {
+  static_assert(DIR == 0 || (GATHER && EDOT && sizeof(TU) == sizeof(TC)),
+                "the direction is formed at the solvers' gather");
   // every array is global memory (the batched kernel reads these pointers
   // from a descriptor, where their address space is not known)
   const gp<const TC> D = (gp<const TC>)D_;
@@ -149,7 +149,22 @@ __device__ __forceinline__ void ax_tile(int t, int64_t e0, int64_t E,
 
   constexpr bool VEC16 = sizeof(TG) == 2 && N1 == 8;  // BF16 column layout
   constexpr bool VECU = sizeof(TU) == 2 && N1 == 8 && !GATHER;
+  constexpr bool FUSE = DIR == 1 || DIR == 2;
+  // the solve's scalars and partial sums are asked for first and waited for
+  // last: waiting for them before the element's loads are issued put a memory
+  // round trip in front of every workgroup
+  DirScalars dsc = {};
+  DirParts<DIR == 2> dparts;
+  if constexpr (DIR != 0) {
+    if (dir != nullptr) {
+      dsc = dir_scalars(dir->st);
+      dparts.load(dir->part, dir->stride, dir->beg, dir->end);
+    }
+  }
   TU ucol[N1];
+  TU pcol[FUSE ? N1 : 1];  // the old direction
+  int64_t dg0 = 0, dgl = 0, dgs = 0;  // FUSE: the column's nodes are dg0 + dgs k, the last dgl
+  bool own_c = false, own_0 = false, own_l = false;  // FUSE: nodes stored by this element
   u32x4 urow = {0u, 0u, 0u, 0u};
   if constexpr (VECU) {
     // lane c reads the 16-byte row (k, j) = (c / 8, c % 8) of the element
@@ -167,7 +182,20 @@ __device__ __forceinline__ void ax_tile(int t, int64_t e0, int64_t E,
     const int64_t g0 = gxy + Gxy * gz0;
 #pragma unroll
     for (int k = 0; k < N1 - 1; ++k) ucol[k] = ld_on ? u[g0 + Gxy * k] : TU(0);
-    ucol[N1 - 1] = ld_on ? u[gxy + Gxy * wrap_coord(gz0 + N1 - 1, box->Gz)] : TU(0);
+    const uint32_t gzl = wrap_coord(gz0 + N1 - 1, box->Gz);
+    ucol[N1 - 1] = ld_on ? u[gxy + Gxy * gzl] : TU(0);
+    if constexpr (FUSE) {
+      const gp<const TU> po = (gp<const TU>)dir->p;
+      dg0 = g0;
+      dgl = gxy + Gxy * gzl;
+      dgs = Gxy;
+#pragma unroll
+      for (int k = 0; k < N1 - 1; ++k) pcol[k] = ld_on ? po[g0 + Gxy * k] : TU(0);
+      pcol[N1 - 1] = ld_on ? po[dgl] : TU(0);
+      own_c = act && owns_coord(i, c3.x, gx) && owns_coord(j, c3.y, gy);
+      own_0 = c3.z == 0;
+      own_l = gzl != 0;
+    }
   } else {
 #pragma unroll
     for (int k = 0; k < N1; ++k) ucol[k] = ld_on ? u[based + k * NP] : TU(0);
@@ -206,10 +234,28 @@ __device__ __forceinline__ void ax_tile(int t, int64_t e0, int64_t E,
   // factor loads, which halves the bytes in flight (165 -> 201 us, FP64,
   // 32^3, N = 7)
   __builtin_amdgcn_sched_barrier(0);
-  // a solver's done flag (uniform over the workgroup) is read only now, with
-  // the element's loads already in flight: waiting for it before them put a
-  // memory round trip in front of every workgroup
-  if (stop != nullptr && *stop != 0) return;
+  if constexpr (DIR == 3) {
+    // (no dir: the caller has looked)
+    if (dir != nullptr && dsc.done != 0) return;  // uniform
+  }
+  if constexpr (FUSE) {
+    const DirStep ds = dir_step<DIR == 2>(dir->st, dsc, dparts, t == 0 && e0 == 0);
+    if (ds.stop) return;  // uniform
+    const TU beta = (TU)ds.beta;
+#pragma unroll
+    for (int k = 0; k < N1; ++k) {
+      // the first iteration has no old direction (its buffer may hold anything)
+      if (!ds.first) ucol[k] = ucol[k] + beta * pcol[k];
+    }
+    if (own_c) {
+      const gp<TU> pn = (gp<TU>)dir->pnew;
+#pragma unroll
+      for (int k = 0; k < N1; ++k) {
+        if (k == 0 ? own_0 : k == N1 - 1 ? own_l : true)
+          pn[k == N1 - 1 ? dgl : dg0 + dgs * k] = ucol[k];
+      }
+    }
+  }
 
   TC uc[N1];
   if constexpr (VECU) {

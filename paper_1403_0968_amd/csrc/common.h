@@ -63,10 +63,40 @@ __device__ inline void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// wave64 sum in a fixed order (butterfly over lanes), deterministic
+// a double moved across the lanes of a wave by a DPP pattern (both halves)
+template <int CTRL> __device__ inline double dpp_f64(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// v plus its value in the other half of the wave (S = 32) or in the
+// neighbouring row of 16 lanes (S = 16): a swap of v's halves (rows) with
+// those of a copy of v leaves one operand of the sum in each copy
+template <int S> __device__ inline double swap_add_f64(double v) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = (unsigned)b, hi = (unsigned)(b >> 32);
+  auto l = S == 32 ? __builtin_amdgcn_permlane32_swap(lo, lo, false, false)
+                   : __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+  auto h = S == 32 ? __builtin_amdgcn_permlane32_swap(hi, hi, false, false)
+                   : __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+  return __longlong_as_double(((long long)h[0] << 32) | l[0]) +
+         __longlong_as_double(((long long)h[1] << 32) | l[1]);
+}
+
+// wave64 sum in a fixed order, the same in every lane: the butterfly over
+// lane distances 32, 16, 8, 4, 2, 1, in registers.  The rotations by 8 and 4
+// within a row reach the lanes at these distances because the partial sums
+// before them repeat with period 16 and 8.  (The same butterfly through
+// ds_bpermute takes an LDS round trip per step.)
 __device__ inline double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+  v = swap_add_f64<32>(v);
+  v = swap_add_f64<16>(v);
+  v += dpp_f64<0x128>(v);  // row_ror:8
+  v += dpp_f64<0x124>(v);  // row_ror:4
+  v += dpp_f64<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+  v += dpp_f64<0xB1>(v);   // quad_perm [1, 0, 3, 2]
   return v;
 }
 

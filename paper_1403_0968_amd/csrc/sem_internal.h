@@ -68,7 +68,9 @@ struct DevBuf {
   template <class T> T *as() const { return static_cast<T *>(p); }
 };
 
-// device-side CG scalars (one struct per solve)
+// device-side CG scalars (one struct per solve); the fields ending in _b are
+// written by the operator and read by the r update, the others the other
+// way round (cg_dir.h)
 struct CgState {
   double rz;      // (r, z)
   double pw;      // (p, A p)
@@ -76,14 +78,21 @@ struct CgState {
   double rr;      // (r, r)
   double bb;      // (b, b)
   double tol2;    // rtol^2
-  double pad0;
+  double rz_b, rr_b;
   int32_t it;     // iterations done
   int32_t maxit;
   int32_t done;   // 0 running, 1 converged, 2 breakdown, 3 maxit, 4 idle
+  int32_t ready;  // 0: beta is still to be formed from the partial sums,
+                  // 1: beta holds it, 2: first iteration (p = z)
+  int32_t it_b, done_b;
   int32_t xupd;   // 1: this iteration's x += alpha p is still to be applied
+                  // (the form with a pass of its own for p and x)
+  int32_t pad0;
 };
 
-// vectors of one solve (unique-node layout except VWL, an E-vector)
+// vectors of one solve (unique-node layout except VWL, an E-vector).  VW, the
+// assembled A x of the initial residuals, is the second direction buffer
+// while CG runs.
 enum { VB = 0, VX, VR, VZ, VP, VW, VWL, NVEC };
 
 // one solve of a batch as the device kernels see it
@@ -171,27 +180,51 @@ void device_setup(sem_handle *h, const sem_mesh_desc *d, hipStream_t s);
 void launch_rhs(sem_handle *h, const sem_source *src, double *b, hipStream_t s);
 void launch_precond(sem_handle *h, int pc, int prec, const void *r, void *z,
                     hipStream_t s);
-// persistent batched operator over (solve, element tile) items; src / dst are
-// vector indices (VP, VX, ..., VWL) of the precision's vector set
-void launch_bax(int prec, int bs, int nset, const BatchSolve *sds,
-                const CgState *st, const AxItem *items, int nitems, int grid,
-                int src, int dst, int skip_done, hipStream_t s);
-// nt: store the output with the streaming hint (vectors beyond the caches)
-void launch_ax_solve(int N, int prec, int64_t E, const void *D, const void *G,
-                     const void *H, const void *u, void *w, const Box &box,
-                     const int32_t *stop, double *edot, bool nt, hipStream_t s);
+// The operator inside the solvers, w_L = A_L Q u into VWL.  mode 0: u is the
+// vector src.  Modes 1 to 3 are one CG iteration, for solves that have not
+// ended, and store the element energies.  mode 3: u is src, the direction.
+// mode 1 or 2 (cg_dir.h): src is VZ and the operator acts on the new
+// direction, its beta from the solve's state (1) or from the partial sums
+// of the last r update (2).
+struct BaxDir {  // the direction arguments of a batch
+  int32_t mode = 0;
+  int32_t par = 0;               // 0: VP holds the old direction, VW the new; 1: swapped
+  const double *part = nullptr;  // [2][stride] partial sums
+  int32_t stride = 0;
+  const int32_t *vbeg = nullptr; // per-solve ranges of the partial sums
+};
+// persistent batched operator over (solve, element tile) items
+void launch_bax(int prec, int bs, int nset, const BatchSolve *sds, CgState *st,
+                const AxItem *items, int nitems, int grid, int src, const BaxDir &bd,
+                hipStream_t s);
+void launch_bax_mfma(int n1, bool split, const BatchSolve *sds, CgState *st,
+                     const AxItem *items, int nitems, int epb, int grid, const BaxDir &bd,
+                     hipStream_t s);
+// a single solve: every argument passed in
+struct SolveAx {
+  int N, prec;
+  int64_t E;
+  const void *D, *Dlo, *G, *H;  // D: D_hi (with Dlo) for the matrix cores
+  const void *u;
+  void *w;
+  Box box;
+  int mode;
+  bool nt;  // store the output with the streaming hint (vectors beyond the caches)
+  // modes 1 to 3
+  const void *p;
+  void *pnew;
+  CgState *st;
+  const double *part;
+  int32_t nparts;
+  double *edot;
+};
+void launch_ax_solve(const SolveAx &a, hipStream_t s);
 void launch_ax_mfma(int N, bool split, int64_t E, const uint16_t *Dhi,
                     const uint16_t *Dlo, const uint16_t *G, const uint16_t *H,
                     const uint16_t *u, float *w, hipStream_t s);
-void launch_bax_mfma(int n1, bool split, const BatchSolve *sds, const CgState *st,
-                     const AxItem *items, int nitems, int epb, int grid, int src,
-                     int dst, int skip_done, bool edot, hipStream_t s);
 // the matrix-core solver operator of a single solve (gathered FP32 input,
-// FP32 output; element energies into edot when non-null)
-void launch_ax_mfma_solve(int N, bool split, int64_t E, const uint16_t *Dhi,
-                          const uint16_t *Dlo, const uint16_t *G, const uint16_t *H,
-                          const float *u, float *w, const Box &box, const int32_t *stop,
-                          double *edot, hipStream_t s);
+// FP32 output)
+void launch_ax_mfma_solve(const SolveAx &a, hipStream_t s);
 int bax_elements_per_tile(int bs, int n1);
 // smallest workgroup (64, 128, 256) holding every (i, j) column of the
 // largest order of an order set

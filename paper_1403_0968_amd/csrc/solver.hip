@@ -11,14 +11,17 @@
 // numbering).  p vanishes on Dirichlet nodes, so (p, w_G) = sum_e p_e^T w_e:
 // the operator stores the element energies and the assembled w_G is never
 // stored -- the r update sums the copies of each node itself (Q^T + mask).
-// One CG iteration of the whole batch is five launches of persistent
-// kernels that walk work lists of (solve, element tile) or (solve, node
-// chunk) items:
+// One CG iteration of the whole batch is two to five launches of kernels
+// that walk work lists of (solve, element tile) or (solve, node chunk)
+// items.  Solves whose vectors stay in the caches:
+//   operator at the new direction p' = z + beta p + element energies
+//   -> [alpha] -> x and r update (assembly of w) + z = dinv r + dots
+//   -> [beta / convergence],
+// where the bracketed scalar kernels run only where many sums are to be
+// added; else the pass after them adds the sums itself (cg_dir.h).  Vectors
+// beyond the caches:
 //   operator + element energies -> alpha -> assembly + r update +
 //   z = dinv r + dots -> beta / convergence -> x and p update.
-// (The matrix-core operator has no energy output: with it the iteration
-// keeps a separate assembly with the (p, w) dot, and r, z and the dots in
-// one more pass.)
 // Scalars stay on the device, one CgState per solve; kernels skip items of
 // solves whose flag says they finished, so a captured HIP graph of K
 // iterations is replayed between host polls without changing any iterate.
@@ -40,12 +43,14 @@
 #include <string>
 
 #include "assemble.h"
+#include "cg_dir.h"
 #include "common.h"
 #include "sem_internal.h"
 
 namespace sem {
 
 constexpr int RT = 256;           // threads of the vector kernels
+static_assert(RT == BT, "cg_dir.h reproduces the sums of the vector kernels' blocks");
 static_assert(VCH % RT == 0, "chunk must be a multiple of the block");
 
 // --------------------------------------------------------------------------
@@ -148,14 +153,14 @@ __global__ void __launch_bounds__(RT)
 
 // alpha_s = rz_s / (p, A p)_s with (p, A p) the sum of the solve's element
 // energies in element order (strided over the workgroup's threads, then the
-// fixed workgroup sum), one workgroup of AT threads per solve
-constexpr int AT = 1024;
+// fixed workgroup sum), one workgroup of AT threads per solve; runs between
+// the operator and the r update
 __global__ void __launch_bounds__(AT)
-    k_balpha_e(const BatchSolve *__restrict__ sds, CgState *st) {
+    k_balpha_e(const BatchSolve *__restrict__ sds, CgState *st, int fused) {
   __shared__ double sm[AT / 64];
   const int s = blockIdx.x;
   if (threadIdx.x == 0) st[s].xupd = 0;  // no x update from an earlier step
-  if (st[s].done != 0) return;
+  if (st[s].done != 0 || (fused && st[s].done_b != 0)) return;
   gp<const double> ed = (gp<const double>)sds[s].edot;
   const int64_t E = sds[s].E;
   constexpr int PF = 32;  // 32768 elements: every energy loaded at once
@@ -173,19 +178,19 @@ __global__ void __launch_bounds__(AT)
   if (threadIdx.x == 0) {
     st[s].pw = pw;
     if (!(pw > 0.0) || !isfinite(pw))
-      st[s].done = 2;
+      (fused ? st[s].done_b : st[s].done) = 2;
     else
-      st[s].alpha = st[s].rz / pw;
+      st[s].alpha = (fused ? st[s].rz_b : st[s].rz) / pw;
   }
 }
 
 // r -= alpha w_G with w_G = mask o Q^T w_L formed here (the copies of each
-// node summed from +0.0 in ascending local index, as the assembly and
-// sem_gs sum them), z = dinv r; partials (r, z), (r, r).  FCG (flexible CG
-// with the learned correction, which the next kernel adds to z): partials
-// (r, z), (z, w_G), (r, r).  xr_asm_chunk updates the chunk [start, start +
-// VCH) of unique nodes; k_bupdate_xr_asm walks the work items of a batch,
-// k_xr_asm_1 the chunks of a single solve.
+// node summed from +0.0 in ascending local index, as the assembly and sem_gs
+// sum them), z = dinv r, and with FUSED x += alpha p'; partials (r, z),
+// (r, r).  FCG (flexible CG with the learned correction, which the next
+// kernel adds to z): partials (r, z), (z, w_G), (r, r).  xr_asm_chunk updates
+// the chunk [start, start + VCH) of unique nodes; k_bupdate_xr_asm walks the
+// work items of a batch, k_xr_asm_1 the chunks of a single solve.
 // a load / store with the streaming (non-temporal) hint when NT
 template <bool NT, class P> __device__ inline auto ld_h(P p) {
   if constexpr (NT)
@@ -200,87 +205,162 @@ template <bool NT, class T, class P> __device__ inline void st_h(T v, P p) {
     *p = v;
 }
 
-template <class TV, class TD, bool FCG, bool PER, bool W64, bool NT>
-__device__ __forceinline__ void xr_asm_chunk(const Box &bx, gp<const TV> wL, gp<TV> r,
-                                             gp<TV> z, gp<const TD> dinv, TV alpha,
-                                             int64_t start, int64_t nG, int q, int nitems,
-                                             double *__restrict__ part, double *sm) {
-  const int64_t end = min(start + (int64_t)VCH, nG);
+// the vectors of one solve in the r update
+template <class TV, class TD> struct XrVecs {
+  gp<const TV> wL, p;
+  gp<TV> x, r, z;
+  gp<const TD> dinv;
+  const double *edot;
+  int64_t E, nG;
+};
+
+struct XrShared {
+  double sm[3][RT / 64], en[AT / 64];
+};
+
+template <class TV, class TD, bool FCG, bool PER, bool W64, int FORM>
+__device__ __forceinline__ void xr_asm_chunk(const Box &bx, const XrVecs<TV, TD> &a,
+                                             CgState *st_, int64_t start, int q, int nitems,
+                                             double *__restrict__ part, XrShared &sh) {
+  constexpr bool FUSED = FORM != 0, RED = FORM == 2, NT = !FUSED;
+  const gp<const CgState> st = (gp<const CgState>)st_;
+  // the step this chunk belongs to (uniform); see CgState for who writes what
+  int done = FUSED ? st->done_b : st->done;
+  if (!FUSED && done != 0) return;
+  const int64_t end = min(start + (int64_t)VCH, a.nG);
   // w_G at the node with coordinates pc (32-bit local indices unless W64:
   // some local index of the batch needs more)
   using IT = typename std::conditional<W64, int64_t, uint32_t>::type;
-  auto assembled = [&](const Coord3 &pc) { return assemble_node<TV, PER, IT>(bx, wL, pc); };
-  double rz = 0.0, rr = 0.0, zw = 0.0;
   constexpr int K = VCH / RT;
   const int64_t g0 = start + threadIdx.x;
-  if (g0 + (K - 1) * RT < end) {
-    // a whole chunk: every load of the thread's K nodes before any store
-    // (the compiler cannot know that w_L, r, z and dinv do not overlap).
-    // NT (a working set beyond the last-level cache): r and dinv stream
-    // non-temporally (next read an iteration later), z is stored normally
-    // for the x / p update right after: FP64 100 -> 87 us at 32^3, N = 7
-    TV sw[K], rv[K];
+  double rz = 0.0, rr = 0.0, zw = 0.0;
+  // WHOLE: all of the chunk's nodes exist; the last chunk's absent ones load
+  // nothing and are not stored.  Returns false when the solve has ended
+  auto run = [&](auto whole_) {
+    constexpr bool WHOLE = decltype(whole_)::value;
+    // every load of the thread's K nodes comes before any store (the compiler
+    // cannot know that the vectors do not overlap) and before the scalars are
+    // waited for.  NT (a working set beyond the last-level cache): r and dinv
+    // stream non-temporally (next read an iteration later), z is stored
+    // normally for the x / p update right after: FP64 100 -> 87 us at 32^3,
+    // N = 7
+    TV sw[K], rv[K], pv[FUSED ? K : 1], xv[FUSED ? K : 1];
     TD dv[K];
+    Energies<RED> en;
+    en.load(a.edot, a.E);
     // the thread's nodes are RT apart: their coordinates advance by carries
     Coord3 pc = box_coord(bx, (uint32_t)g0);
     const Coord3 step = box_coord(bx, (uint32_t)RT);
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      sw[k] = assembled(pc);
-      rv[k] = ld_h<NT>(r + g0 + k * RT);
-      dv[k] = ld_h<NT>(dinv + g0 + k * RT);
+      const int64_t g = g0 + k * RT;
+      if constexpr (!WHOLE) {
+        sw[k] = rv[k] = TV(0);
+        dv[k] = TD(0);
+        if constexpr (FUSED) pv[k] = xv[k] = TV(0);
+      }
+      if (WHOLE || g < end) {
+        sw[k] = assemble_node<TV, PER, IT>(bx, a.wL, pc);
+        rv[k] = ld_h<NT>(a.r + g);
+        dv[k] = ld_h<NT>(a.dinv + g);
+        if constexpr (FUSED) {
+          pv[k] = a.p[g];
+          xv[k] = a.x[g];
+        }
+      }
       box_advance(bx, step, pc);
     }
+    double alpha = 0.0;
+    if constexpr (FUSED) {
+      double pw = 0.0;
+      const double rz_b = st->rz_b;
+      if constexpr (RED) {
+        if (done == 0) {
+          pw = en.sum(sh.en);
+          alpha = rz_b / pw;
+          if (!(pw > 0.0) || !isfinite(pw)) done = 2;
+        }
+      } else {
+        alpha = st->alpha;
+      }
+      if (start == 0 && threadIdx.x == 0) {
+        const gp<CgState> w = (gp<CgState>)st_;
+        w->it = st->it_b;
+        w->rr = st->rr_b;
+        w->rz = rz_b;
+        w->done = done;
+        w->ready = 0;
+        if (RED && done == 0) w->pw = pw;
+      }
+      if (done != 0) return false;
+    } else {
+      alpha = st->alpha;
+    }
+    const TV al = (TV)alpha;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      const TV rn = rv[k] - alpha * sw[k];
-      st_h<NT>(rn, r + g0 + k * RT);
-      const TV zn = (TV)(dv[k] * rn);
-      z[g0 + k * RT] = zn;
-      rz += (double)rn * (double)zn;
-      rr += (double)rn * (double)rn;
-      if constexpr (FCG) zw += (double)zn * (double)sw[k];
+      const int64_t g = g0 + k * RT;
+      if (WHOLE || g < end) {
+        if constexpr (FUSED) a.x[g] = xv[k] + al * pv[k];
+        const TV rn = rv[k] - al * sw[k];
+        st_h<NT>(rn, a.r + g);
+        const TV zn = (TV)(dv[k] * rn);
+        a.z[g] = zn;
+        rz += (double)rn * (double)zn;
+        rr += (double)rn * (double)rn;
+        if constexpr (FCG) zw += (double)zn * (double)sw[k];
+      }
     }
+    return true;
+  };
+  if (start + VCH <= a.nG) {  // uniform
+    if (!run(std::true_type())) return;
   } else {
-    for (int64_t g = g0; g < end; g += RT) {
-      const TV sg = assembled(box_coord(bx, (uint32_t)g));
-      const TV rn = r[g] - alpha * sg;
-      r[g] = rn;
-      const TV zn = (TV)(dinv[g] * rn);
-      z[g] = zn;
-      rz += (double)rn * (double)zn;
-      rr += (double)rn * (double)rn;
-      if constexpr (FCG) zw += (double)zn * (double)sg;
-    }
+    if (!run(std::false_type())) return;
   }
-  const double trz = block_sum<RT>(rz, sm);
-  const double trr = block_sum<RT>(rr, sm);
-  const double tzw = FCG ? block_sum<RT>(zw, sm) : 0.0;
-  if (threadIdx.x == 0) {
-    part[q] = trz;
-    if constexpr (FCG) {
-      part[nitems + q] = tzw;
-      part[2 * nitems + q] = trr;
-    } else {
-      part[nitems + q] = trr;
-    }
+  // the workgroup's sums, as block_sum adds them, with one barrier for all
+  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  rz = wave_sum(rz);
+  rr = wave_sum(rr);
+  if constexpr (FCG) zw = wave_sum(zw);
+  if (lane == 0) {
+    sh.sm[0][wv] = rz;
+    sh.sm[1][wv] = FCG ? zw : rr;
+    if constexpr (FCG) sh.sm[2][wv] = rr;
+  }
+  __syncthreads();
+  constexpr int NS = FCG ? 3 : 2;
+  if (threadIdx.x < NS) {
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < RT / 64; ++w) s += sh.sm[threadIdx.x][w];
+    part[(int)threadIdx.x * nitems + q] = s;
   }
 }
 
-template <class TV, class TD, bool FCG, bool PER, bool W64, bool NT>
+// FORM: 0 the r update alone, 1 with the x update, 2 also with the sum of
+// the element energies.  par: which of VP and VW holds the new direction in
+// forms 1 and 2 (VW when 0)
+template <class TV, class TD, bool PER, bool W64, int FORM>
 __global__ void __launch_bounds__(RT)
-    k_bupdate_xr_asm(const BatchSolve *__restrict__ sds,
-                     const CgState *__restrict__ st,
+    k_bupdate_xr_asm(const BatchSolve *__restrict__ sds, CgState *st,
                      const VecItem *__restrict__ items, int nitems,
-                     double *__restrict__ part, int jac) {
-  __shared__ double sm[RT / 64];
+                     double *__restrict__ part, int jac, int par) {
+  __shared__ XrShared sh;
   for (int q = blockIdx.x; q < nitems; q += gridDim.x) {
     const VecItem it = items[q];
-    if (st[it.solve].done != 0) continue;
+    // the writer's chunk of a finished solve goes on, to record the flag
+    if (FORM ? st[it.solve].done_b != 0 && it.start != 0 : st[it.solve].done != 0)
+      continue;  // uniform
     const BatchSolve &sd = sds[it.solve];
-    xr_asm_chunk<TV, TD, FCG, PER, W64, NT>(
-        sd.box, vec<TV>(sd, VWL), vec<TV>(sd, VR), vec<TV>(sd, VZ), dinv_of<TD>(sd, jac),
-        (TV)st[it.solve].alpha, it.start, sd.nG, q, nitems, part, sm);
+    const XrVecs<TV, TD> a = {vec<TV>(sd, VWL), vec<TV>(sd, par ? VP : VW),
+                              vec<TV>(sd, VX),  vec<TV>(sd, VR),
+                              vec<TV>(sd, VZ),  dinv_of<TD>(sd, jac),
+                              sd.edot,          sd.E,
+                              sd.nG};
+    xr_asm_chunk<TV, TD, false, PER, W64, FORM>(sd.box, a, st + it.solve, it.start, q,
+                                                   nitems, part, sh);
+    __syncthreads();  // sh is used again by the next item
   }
 }
 
@@ -290,26 +370,27 @@ __global__ void __launch_bounds__(RT)
 // solve's descriptor (a chain of dependent loads in front of every chunk)
 template <class TV, class TD> struct Vecs1 {
   Box box;
-  int64_t nG;
+  int64_t nG, E;
   const TV *wL;
-  TV *r, *z, *p, *x;
+  TV *p;  // the direction (FUSED: the new one)
+  TV *r, *z, *x;
   const TD *dinv;
+  const double *edot;
 };
 
-template <class TV, class TD, bool FCG, bool PER, bool W64, bool NT>
+template <class TV, class TD, bool FCG, bool PER, bool W64, int FORM>
 __global__ void __launch_bounds__(RT)
-    k_xr_asm_1(Vecs1<TV, TD> a, const CgState *__restrict__ st, int nitems,
-               double *__restrict__ part) {
-  __shared__ double sm[RT / 64];
-  if (st->done != 0) return;
+    k_xr_asm_1(Vecs1<TV, TD> v, CgState *st, int nitems, double *__restrict__ part) {
+  __shared__ XrShared sh;
   const int q = blockIdx.x;
-  xr_asm_chunk<TV, TD, FCG, PER, W64, NT>(a.box, (gp<const TV>)a.wL, (gp<TV>)a.r,
-                                          (gp<TV>)a.z, (gp<const TD>)a.dinv,
-                                          (TV)st->alpha, (int64_t)q * VCH, a.nG, q,
-                                          nitems, part, sm);
+  const XrVecs<TV, TD> a = {(gp<const TV>)v.wL, (gp<const TV>)v.p, (gp<TV>)v.x,
+                            (gp<TV>)v.r,        (gp<TV>)v.z,       (gp<const TD>)v.dinv,
+                            v.edot,             v.E,               v.nG};
+  xr_asm_chunk<TV, TD, FCG, PER, W64, FORM>(v.box, a, st, (int64_t)q * VCH, q, nitems,
+                                               part, sh);
 }
 
-// rz, rr per solve -> convergence / beta
+// rz, rr per solve -> convergence / beta (cg_dir.h reproduces its sums)
 __global__ void __launch_bounds__(RT)
     k_bbeta(CgState *st, const double *__restrict__ part,
             const int32_t *__restrict__ vbeg, int nitems) {
@@ -318,30 +399,25 @@ __global__ void __launch_bounds__(RT)
   if (st[s].done != 0) return;
   double acc[2];
   strided_sums<2>(part, nitems, vbeg[s], vbeg[s + 1], acc);
-  const double a = acc[0], b = acc[1];
-  const double rz = block_sum<RT>(a, sm);
-  const double rr = block_sum<RT>(b, sm);
+  const double rz = block_sum<RT>(acc[0], sm);
+  const double rr = block_sum<RT>(acc[1], sm);
   if (threadIdx.x == 0) {
     CgState &c = st[s];
     c.xupd = 1;  // this step's alpha is finite: x += alpha p follows
     c.it += 1;
     c.rr = rr;
-    if (!isfinite(rr) || !isfinite(rz))
-      c.done = 2;
-    else if (rr <= c.tol2 * c.bb)
-      c.done = 1;
-    else if (c.it >= c.maxit)
-      c.done = 3;
-    else {
+    c.done = cg_verdict(rz, rr, c.tol2, c.bb, c.it, c.maxit);
+    if (c.done == 0) {
       c.beta = rz / c.rz;
       c.rz = rz;
+      c.ready = 1;
     }
   }
 }
 
 // x += alpha p with this step's alpha (when k_bbeta found it finite, also
 // on the step that converged), then p = z + beta p while the solve runs
-template <class TV, bool NT>
+template <class TV>
 __device__ __forceinline__ void p_chunk(gp<const TV> z, gp<TV> p, gp<TV> x, TV alpha,
                                         TV beta, bool run, int64_t start, int64_t nG) {
   const int64_t end = min(start + (int64_t)VCH, nG);
@@ -350,7 +426,7 @@ __device__ __forceinline__ void p_chunk(gp<const TV> z, gp<TV> p, gp<TV> x, TV a
   if (run && g0 + (K - 1) * RT < end) {
     // a whole chunk: every load of the thread's K nodes before any store
     // (the compiler cannot know that x, p and z do not overlap): 78 -> 67
-    // us at 11.4M unique nodes in FP64.  NT: x and z stream non-temporally
+    // us at 11.4M unique nodes in FP64.  x and z stream non-temporally
     // (x is next read an iteration later, z not again); p (gathered by the
     // next operator) keeps the normal hint, so that it can stay in the
     // last-level cache
@@ -358,12 +434,12 @@ __device__ __forceinline__ void p_chunk(gp<const TV> z, gp<TV> p, gp<TV> x, TV a
 #pragma unroll
     for (int k = 0; k < K; ++k) {
       pv[k] = p[g0 + k * RT];
-      xv[k] = ld_h<NT>(x + g0 + k * RT);
-      zv[k] = ld_h<NT>(z + g0 + k * RT);
+      xv[k] = ld_h<true>(x + g0 + k * RT);
+      zv[k] = ld_h<true>(z + g0 + k * RT);
     }
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      st_h<NT>(xv[k] + alpha * pv[k], x + g0 + k * RT);
+      st_h<true>(xv[k] + alpha * pv[k], x + g0 + k * RT);
       p[g0 + k * RT] = zv[k] + beta * pv[k];
     }
   } else if (run) {
@@ -377,7 +453,7 @@ __device__ __forceinline__ void p_chunk(gp<const TV> z, gp<TV> p, gp<TV> x, TV a
   }
 }
 
-template <class TV, bool NT>
+template <class TV>
 __global__ void __launch_bounds__(RT)
     k_bupdate_p(const BatchSolve *__restrict__ sds, const CgState *__restrict__ st,
                 const VecItem *__restrict__ items, int nitems) {
@@ -386,18 +462,18 @@ __global__ void __launch_bounds__(RT)
     const CgState &c = st[it.solve];
     if (c.xupd == 0) continue;  // uniform per item
     const BatchSolve &sd = sds[it.solve];
-    p_chunk<TV, NT>(vec<TV>(sd, VZ), vec<TV>(sd, VP), vec<TV>(sd, VX), (TV)c.alpha,
+    p_chunk<TV>(vec<TV>(sd, VZ), vec<TV>(sd, VP), vec<TV>(sd, VX), (TV)c.alpha,
                     (TV)c.beta, c.done == 0, it.start, sd.nG);
   }
 }
 
 // the same for the chunks of a single solve
-template <class TV, class TD, bool NT>
+template <class TV, class TD>
 __global__ void __launch_bounds__(RT)
     k_p_1(Vecs1<TV, TD> a, const CgState *__restrict__ st) {
   const CgState &c = *st;
   if (c.xupd == 0) return;
-  p_chunk<TV, NT>((gp<const TV>)a.z, (gp<TV>)a.p, (gp<TV>)a.x, (TV)c.alpha, (TV)c.beta,
+  p_chunk<TV>((gp<const TV>)a.z, (gp<TV>)a.p, (gp<TV>)a.x, (TV)c.alpha, (TV)c.beta,
                   c.done == 0, (int64_t)blockIdx.x * VCH, a.nG);
 }
 
@@ -455,9 +531,9 @@ __global__ void __launch_bounds__(RT)
   CgState &c = st[s];
   if (!active[s]) {
     if (threadIdx.x == 0) {
-      c.done = 4;
-      c.it = 0;
+      c.done = c.done_b = 4;
       c.xupd = 0;
+      c.it = c.it_b = 0;
     }
     return;
   }
@@ -474,7 +550,9 @@ __global__ void __launch_bounds__(RT)
     c.tol2 = tol2;
     c.it = 0;
     c.maxit = maxit[s];
+    c.ready = 2;
     c.xupd = 0;
+    c.done_b = 0;
     c.alpha = c.beta = c.pw = 0.0;
     if (!isfinite(rr) || !isfinite(rz))
       c.done = 2;
@@ -631,15 +709,11 @@ __global__ void __launch_bounds__(RT)
     cs.xupd = 1;  // this step's alpha is finite: x += alpha p follows
     cs.it += 1;
     cs.rr = rr;
-    if (!isfinite(rr) || !isfinite(rz) || !isfinite(zw))
-      cs.done = 2;
-    else if (rr <= cs.tol2 * cs.bb)
-      cs.done = 1;
-    else if (cs.it >= cs.maxit)
-      cs.done = 3;
-    else {
+    cs.done = isfinite(zw) ? cg_verdict(rz, rr, cs.tol2, cs.bb, cs.it, cs.maxit) : 2;
+    if (cs.done == 0) {
       cs.beta = -zw / cs.pw;
       cs.rz = rz;
+      cs.ready = 1;
     }
   }
 }
@@ -756,6 +830,7 @@ struct sem_batch {
   int n_vi_c = 0, n_ax_c[3] = {0, 0, 0};
   bool compact = false;         // the iteration kernels use the compacted lists
   int list_ver = 0;             // version of the compacted lists
+  int par = 0;                  // direction buffers: 0 old VP, new VW; 1 swapped
   std::vector<sem::VecItem> h_vis;
   std::vector<sem::AxItem> h_ax[3];
   std::vector<int32_t> h_vbeg, h_axbeg[3];  // per-solve item ranges
@@ -774,7 +849,7 @@ struct sem_batch {
   hipStream_t s = nullptr;
   hipEvent_t ev0 = nullptr, ev1 = nullptr, fence = nullptr;
   struct GraphEntry {
-    int prec, k, jac, mode, ver;  // ver: list version (0: the full lists)
+    int prec, k, jac, mode, par, ver;  // ver: list version (0: the full lists)
     hipGraphExec_t exec;
   };
   // snapshot recording of solve 0 (training data), FP64 unique vectors
@@ -998,19 +1073,6 @@ static int it_nax(const sem_batch *b, int k) { return b->compact ? b->n_ax_c[k] 
     }                                                      \
   } while (0)
 
-// launch a vector kernel in its variant with (NT_ = true) or without the
-// streaming hints (stream_vectors)
-#define SEM_NT_LAUNCH(NT, KERNEL, ...)                     \
-  do {                                                     \
-    if (NT) {                                              \
-      constexpr bool NT_ = true;                           \
-      hipLaunchKernelGGL(KERNEL, __VA_ARGS__);             \
-    } else {                                               \
-      constexpr bool NT_ = false;                          \
-      hipLaunchKernelGGL(KERNEL, __VA_ARGS__);             \
-    }                                                      \
-  } while (0)
-
 // the same, with W64_ = true when some local index of the batch needs more
 // than 32 bits
 #define SEM_ASM_LAUNCH(B, KERNEL, ...)                     \
@@ -1024,117 +1086,163 @@ static int it_nax(const sem_batch *b, int k) { return b->compact ? b->n_ax_c[k] 
     }                                                      \
   } while (0)
 
-// the same, also choosing the variant with (NT_ = true) or without the
-// streaming hints
-#define SEM_ASM_NT_LAUNCH(B, NT, KERNEL, ...)              \
-  do {                                                     \
-    if (NT) {                                              \
-      constexpr bool NT_ = true;                           \
-      SEM_ASM_LAUNCH(B, KERNEL, __VA_ARGS__);              \
-    } else {                                               \
-      constexpr bool NT_ = false;                          \
-      SEM_ASM_LAUNCH(B, KERNEL, __VA_ARGS__);              \
-    }                                                      \
-  } while (0)
+// The scalar kernels are left out where the passes after them can add the
+// sums up themselves for less than a launch costs (about 5 us): the bytes
+// that all waves (operator) or workgroups (r update) then read from the L2
+// stay below RED_BYTES, and no solve has more entries than a wave or
+// workgroup loads at once (RED_PARTS, RED_ENERGIES).
+constexpr double RED_BYTES = 32.0 * 1024 * 1024;
 
-// the operator of every solve of the batch, w_L = A_L Q v_src into VWL;
-// edot: the single-solve kernel also stores the element energies (the
-// batched kernel always does)
-static void bax(sem_batch *b, int prec, int src, int dst, int skip_done,
-                bool edot = false) {
-  if (prec == SEM_BF16_MFMA || prec == SEM_BF16_PLAIN_D) {
-    // matrix-core operator: tiles of the 256-thread item list, one order
-    if (b->nset < 2 || b->nset > 9)
-      fail(SEM_ERR_ARG, "solve: the matrix-core operator needs solves of one "
-                        "order N <= 8");
-    if (b->n == 1) {  // a single solve: every argument passed in
-      const BatchSolve &d = b->hsd[0];
-      const int32_t *stop =
-          skip_done ? &b->st.as<CgState>()[0].done : (const int32_t *)nullptr;
-      launch_ax_mfma_solve(d.N1 - 1, prec == SEM_BF16_MFMA, d.E, (const uint16_t *)d.D16hi,
-                           (const uint16_t *)d.D16lo, (const uint16_t *)d.G16,
-                           (const uint16_t *)d.H16, (const float *)d.v32[src],
-                           (float *)d.v32[dst], d.box, stop, edot ? d.edot : nullptr, b->s);
-      return;
-    }
-    const int k = bs_slot(256);
-    launch_bax_mfma(b->nset, prec == SEM_BF16_MFMA, b->sds.as<BatchSolve>(),
-                    b->st.as<CgState>(), it_axitems(b, k), it_nax(b, k),
-                    bax_elements_per_tile(256, b->nset), it_nax(b, k), src, dst,
-                    skip_done, edot, b->s);
-    return;
+// whether the operator forms beta from the partial sums of the r update
+static bool reduce_parts(const sem_batch *b) {
+  double bytes = 0.0;
+  for (int q = 0; q < b->n; ++q) {
+    const BatchSolve &d = b->hsd[q];
+    const int64_t nv = (d.nG + VCH - 1) / VCH;
+    if (nv > RED_PARTS) return false;
+    const double waves = (double)d.E * std::max(1.0, d.N1 * d.N1 / 64.0);
+    bytes += 16.0 * (double)nv * waves;
   }
-  if (b->n == 1) {
-    // a single solve: the operator with every argument in registers
-    sem_handle *h = b->hs[0];
+  return bytes <= RED_BYTES;
+}
+
+// whether the r update forms alpha from the element energies
+static bool reduce_energies(const sem_batch *b) {
+  double bytes = 0.0;
+  for (int q = 0; q < b->n; ++q) {
+    const BatchSolve &d = b->hsd[q];
+    if (d.E > RED_ENERGIES) return false;
+    bytes += 8.0 * (double)d.E * (double)((d.nG + VCH - 1) / VCH);
+  }
+  return bytes <= RED_BYTES;
+}
+
+// the operator of every solve of the batch, w_L = A_L Q u into VWL: u the
+// vector src (mode 0), or the new direction of a CG iteration (BaxDir)
+static void bax(sem_batch *b, int prec, int src, int mode) {
+  const bool mfma = prec == SEM_BF16_MFMA || prec == SEM_BF16_PLAIN_D;
+  if (mfma && (b->nset < 2 || b->nset > 9))
+    fail(SEM_ERR_ARG, "solve: the matrix-core operator needs solves of one "
+                      "order N <= 8");
+  CgState *st = b->st.as<CgState>();
+  const double *part = b->part.as<double>();
+  if (b->n == 1) {  // a single solve: every argument passed in
     const BatchSolve &d = b->hsd[0];
+    sem_handle *h = b->hs[0];
     const bool f64 = prec == SEM_FP64;
-    const void *G = f64 ? h->G64.p : prec == SEM_FP32 ? h->G32.p : h->G16.p;
-    const void *H = !h->has_mass ? nullptr
-                    : f64        ? h->H64.p
-                    : prec == SEM_FP32 ? h->H32.p
-                                       : h->H16.p;
-    const void *D = f64 ? h->D64.p : h->D32.p;
-    const void *u = f64 ? d.v64[src] : d.v32[src];
-    void *w = f64 ? d.v64[dst] : d.v32[dst];
-    const int32_t *stop =
-        skip_done ? &b->st.as<CgState>()[0].done : (const int32_t *)nullptr;
-    launch_ax_solve(h->N, prec, h->E, D, G, H, u, w,
-                    make_box(h->N, h->ex, h->ey, h->ez, h->dirichlet, h->periodic), stop,
-                    edot ? d.edot : nullptr, stream_vectors(b, f64 ? 8 : 4) != 0, b->s);
+    auto v = [&](int i) { return f64 ? d.v64[i] : d.v32[i]; };
+    SolveAx a{};
+    a.N = h->N;
+    a.prec = prec;
+    a.E = h->E;
+    a.D = f64 ? h->D64.p : mfma ? h->D16hi.p : h->D32.p;
+    a.Dlo = h->D16lo.p;
+    a.G = f64 ? h->G64.p : prec == SEM_FP32 ? h->G32.p : h->G16.p;
+    a.H = !h->has_mass ? nullptr : f64 ? h->H64.p : prec == SEM_FP32 ? h->H32.p : h->H16.p;
+    a.u = v(src);
+    a.w = v(VWL);
+    a.box = d.box;
+    a.mode = mode;
+    a.nt = stream_vectors(b, f64 ? 8 : 4) != 0;
+    a.p = v(b->par ? VW : VP);
+    a.pnew = v(b->par ? VP : VW);
+    a.st = st;
+    a.part = part;
+    a.nparts = b->n_vi;
+    a.edot = d.edot;
+    if (mfma)
+      launch_ax_mfma_solve(a, b->s);
+    else
+      launch_ax_solve(a, b->s);
     return;
   }
-  const int bs = b->bs[prec];
+  BaxDir bd;
+  bd.mode = mode;
+  bd.par = b->par;
+  bd.part = part;
+  bd.stride = it_nvi(b);
+  bd.vbeg = it_vbeg(b);
+  // the matrix-core operator takes the tiles of the 256-thread item list
+  const int bs = mfma ? 256 : b->bs[prec];
   const int k = bs_slot(bs);
   const int n = it_nax(b, k);
+  if (mfma) {
+    launch_bax_mfma(b->nset, prec == SEM_BF16_MFMA, b->sds.as<BatchSolve>(), st,
+                    it_axitems(b, k), n, bax_elements_per_tile(256, b->nset), n, bd, b->s);
+    return;
+  }
   const int grid = b->gmul[prec] > 0 ? std::min(n, 256 * b->gmul[prec]) : n;
-  launch_bax(prec, bs, b->nset, b->sds.as<BatchSolve>(), b->st.as<CgState>(),
-             it_axitems(b, k), n, grid, src, dst, skip_done, b->s);
+  launch_bax(prec, bs, b->nset, b->sds.as<BatchSolve>(), st, it_axitems(b, k), n, grid, src,
+             bd, b->s);
 }
 
 // the single-solve kernels' view of the batch's one solve
 template <class TV, class TD>
-static Vecs1<TV, TD> vecs1(const sem_batch *b, int jac) {
+static Vecs1<TV, TD> vecs1(const sem_batch *b, int jac, bool fused) {
   const BatchSolve &d = b->hsd[0];
   auto v = [&](int i) { return (TV *)(sizeof(TV) == 8 ? d.v64[i] : d.v32[i]); };
   Vecs1<TV, TD> a;
   a.box = d.box;
   a.nG = d.nG;
+  a.E = d.E;
   a.wL = v(VWL);
   a.r = v(VR);
   a.z = v(VZ);
-  a.p = v(VP);
+  a.p = v(fused ? (b->par ? VP : VW) : VP);
   a.x = v(VX);
+  a.edot = d.edot;
   a.dinv = (const TD *)(sizeof(TD) == 8 ? (jac ? (const void *)d.dinv64 : d.one64)
                                         : (jac ? (const void *)d.dinv32 : d.one32));
   return a;
 }
 
+// launch the r update in its form (k_bupdate_xr_asm)
+#define SEM_XR_LAUNCH(B, FORM, KERNEL, ...)                \
+  do {                                                     \
+    if ((FORM) == 0) {                                     \
+      constexpr int FORM_ = 0;                             \
+      SEM_ASM_LAUNCH(B, KERNEL, __VA_ARGS__);              \
+    } else if ((FORM) == 1) {                              \
+      constexpr int FORM_ = 1;                             \
+      SEM_ASM_LAUNCH(B, KERNEL, __VA_ARGS__);              \
+    } else {                                               \
+      constexpr int FORM_ = 2;                             \
+      SEM_ASM_LAUNCH(B, KERNEL, __VA_ARGS__);              \
+    }                                                      \
+  } while (0)
+
+// One iteration (see the head of this file); last: no iteration follows in
+// this launch sequence, so that beta and the convergence flag are brought up
+// to date for the host.  The state's sums go to the same bits whichever
+// kernel adds them.
 template <class TV, class TD>
-static void iteration_t(sem_batch *b, int prec, int jac) {
+static void iteration_t(sem_batch *b, int prec, int jac, bool last) {
   const BatchSolve *sds = b->sds.as<BatchSolve>();
   CgState *st = b->st.as<CgState>();
-  const VecItem *vi = it_vitems(b);
   double *part = b->part.as<double>();
-  const int32_t *vbeg = it_vbeg(b);
-  const int nv = it_nvi(b), g = nv, n = b->n;
-  // (p, A p) from the operator's element energies (every operator form, the
-  // matrix-core one included, stores them)
-  const bool nt = stream_vectors(b, sizeof(TV)) != 0;
-  bax(b, prec, VP, VWL, 1, true);
-  hipLaunchKernelGGL(k_balpha_e, dim3(n), dim3(AT), 0, b->s, sds, st);
-  if (b->n == 1)
-    SEM_ASM_NT_LAUNCH(b, nt, (k_xr_asm_1<TV, TD, false, PER_, W64_, NT_>), dim3(nv),
-                      dim3(RT), 0, b->s, vecs1<TV, TD>(b, jac), st, nv, part);
+  const VecItem *vi = it_vitems(b);
+  const int nv = it_nvi(b), n = b->n;
+  const bool fused = stream_vectors(b, sizeof(TV)) == 0;
+  const bool redp = fused && reduce_parts(b), rede = fused && reduce_energies(b);
+  const int form = !fused ? 0 : rede ? 2 : 1;
+  bax(b, prec, fused ? VZ : VP, !fused ? 3 : redp ? 2 : 1);
+  if (!rede)
+    hipLaunchKernelGGL(k_balpha_e, dim3(n), dim3(AT), 0, b->s, sds, st, fused ? 1 : 0);
+  if (n == 1)
+    SEM_XR_LAUNCH(b, form, (k_xr_asm_1<TV, TD, false, PER_, W64_, FORM_>), dim3(nv),
+                  dim3(RT), 0, b->s, vecs1<TV, TD>(b, jac, fused), st, nv, part);
   else
-    SEM_ASM_NT_LAUNCH(b, nt, (k_bupdate_xr_asm<TV, TD, false, PER_, W64_, NT_>), dim3(g),
-                      dim3(RT), 0, b->s, sds, st, vi, nv, part, jac);
-  hipLaunchKernelGGL(k_bbeta, dim3(n), dim3(RT), 0, b->s, st, part, vbeg, nv);
-  if (b->n == 1)
-    SEM_NT_LAUNCH(nt, (k_p_1<TV, TD, NT_>), dim3(nv), dim3(RT), 0, b->s,
-                  vecs1<TV, TD>(b, jac), st);
+    SEM_XR_LAUNCH(b, form, (k_bupdate_xr_asm<TV, TD, PER_, W64_, FORM_>), dim3(nv),
+                  dim3(RT), 0, b->s, sds, st, vi, nv, part, jac, b->par);
+  if (last || !redp)
+    hipLaunchKernelGGL(k_bbeta, dim3(n), dim3(RT), 0, b->s, st, part, it_vbeg(b), nv);
+  if (fused)
+    b->par ^= 1;
+  else if (n == 1)
+    hipLaunchKernelGGL((k_p_1<TV, TD>), dim3(nv), dim3(RT), 0, b->s,
+                       vecs1<TV, TD>(b, jac, fused), st);
   else
-    SEM_NT_LAUNCH(nt, (k_bupdate_p<TV, NT_>), dim3(g), dim3(RT), 0, b->s, sds, st, vi, nv);
+    hipLaunchKernelGGL((k_bupdate_p<TV>), dim3(nv), dim3(RT), 0, b->s, sds, st, vi, nv);
   SEM_HIP(hipGetLastError());
 }
 
@@ -1150,35 +1258,42 @@ static void iteration_fcg_t(sem_batch *b, int prec) {
   const int nv = b->n_vi, n = b->n;
   sem_handle *h = b->hs[0];
   const bool f32 = sizeof(TV) == 4;
-  const bool nt = stream_vectors(b, sizeof(TV)) != 0;
-  bax(b, prec, VP, VWL, 1, true);
-  hipLaunchKernelGGL(k_balpha_e, dim3(n), dim3(AT), 0, b->s, b->sds.as<BatchSolve>(), st);
-  SEM_ASM_NT_LAUNCH(b, nt, (k_xr_asm_1<TV, TD, true, PER_, W64_, NT_>), dim3(nv), dim3(RT),
-                    0, b->s, vecs1<TV, TD>(b, 1), st, nv, part);
+  const bool fused = stream_vectors(b, sizeof(TV)) == 0;
+  const bool rede = fused && reduce_energies(b);
+  bax(b, prec, fused ? VZ : VP, fused ? 1 : 3);
+  if (!rede)
+    hipLaunchKernelGGL(k_balpha_e, dim3(n), dim3(AT), 0, b->s, b->sds.as<BatchSolve>(), st,
+                       fused ? 1 : 0);
+  SEM_XR_LAUNCH(b, !fused ? 0 : rede ? 2 : 1,
+                (k_xr_asm_1<TV, TD, true, PER_, W64_, FORM_>), dim3(nv), dim3(RT), 0,
+                b->s, vecs1<TV, TD>(b, 1, fused), st, nv, part);
   const BatchSolve &d = b->hsd[0];
   learn_apply_fused(h, f32 ? d.v32[VR] : d.v64[VR], f32 ? d.v32[VZ] : d.v64[VZ],
                     f32 ? d.v32[VWL] : d.v64[VWL], f32, b->s);
   hipLaunchKernelGGL(k_bbeta_fcg_e, dim3(1), dim3(RT), 0, b->s, st, part, nv,
                      learn_epart(h), (int)h->E);
-  SEM_NT_LAUNCH(nt, (k_p_1<TV, TD, NT_>), dim3(nv), dim3(RT), 0, b->s, vecs1<TV, TD>(b, 1),
-                st);
+  if (fused)
+    b->par ^= 1;
+  else
+    hipLaunchKernelGGL((k_p_1<TV, TD>), dim3(nv), dim3(RT), 0, b->s,
+                       vecs1<TV, TD>(b, 1, fused), st);
   SEM_HIP(hipGetLastError());
 }
 
-// mode 0: PCG with the `jac` preconditioner; mode 1: flexible CG with the
-// learned correction
-static void iteration(sem_batch *b, int prec, int jac, int mode = 0) {
-  if (mode == 1) {
-    if (prec == SEM_FP64)
+// K iterations; mode 0: PCG with the `jac` preconditioner; mode 1: flexible
+// CG with the learned correction
+static void iterations(sem_batch *b, int prec, int K, int jac, int mode) {
+  for (int q = 0; q < K; ++q) {
+    const bool last = q + 1 == K;
+    if (mode == 1 && prec == SEM_FP64)
       iteration_fcg_t<double, double>(b, prec);
-    else
+    else if (mode == 1)
       iteration_fcg_t<float, float>(b, prec);
-    return;
+    else if (prec == SEM_FP64)
+      iteration_t<double, double>(b, prec, jac, last);
+    else
+      iteration_t<float, float>(b, prec, jac, last);
   }
-  if (prec == SEM_FP64)
-    iteration_t<double, double>(b, prec, jac);
-  else
-    iteration_t<float, float>(b, prec, jac);
 }
 
 float *learn_cg(sem_handle *h);
@@ -1218,9 +1333,10 @@ static void init(sem_batch *b, int prec, int jac, bool x0_zero, double tol2) {
   double *part = b->part.as<double>();
   const int g = vec_grid(b), nv = b->n_vi;
   const int32_t *act = b->active.as<int32_t>();
+  b->par = 0;
   if (!x0_zero) {
     // w = A x (FP64 only)
-    bax(b, SEM_FP64, VX, VWL, 0);
+    bax(b, SEM_FP64, VX, 0);
     SEM_PER_LAUNCH(b, (k_bassemble<double, false, PER_>), dim3(g), dim3(RT), 0, b->s,
                        sds, b->st.as<CgState>(), vi, nv, part, 0);
   }
@@ -1244,7 +1360,7 @@ static void residual(sem_batch *b) {
   double *part = b->part.as<double>();
   const int g = vec_grid(b), nv = b->n_vi;
   const int32_t *act = b->active.as<int32_t>();
-  bax(b, SEM_FP64, VX, VWL, 0);
+  bax(b, SEM_FP64, VX, 0);
   SEM_PER_LAUNCH(b, (k_bassemble<double, false, PER_>), dim3(g), dim3(RT), 0, b->s, sds,
                      b->st.as<CgState>(), vi, nv, part, 0);
   hipLaunchKernelGGL(k_bresidual, dim3(g), dim3(RT), 0, b->s, sds, act, vi, nv,
@@ -1271,15 +1387,18 @@ static void upload_active(sem_batch *b, const std::vector<int> &act,
 
 static hipGraphExec_t get_graph(sem_batch *b, int prec, int K, int jac,
                                 int mode) {
-  const int ver = b->compact ? b->list_ver : 0;
+  const int ver = b->compact ? b->list_ver : 0, par = b->par;
   for (auto &g : b->graphs)
-    if (g.prec == prec && g.k == K && g.jac == jac && g.mode == mode && g.ver == ver)
+    if (g.prec == prec && g.k == K && g.jac == jac && g.mode == mode && g.par == par &&
+        g.ver == ver)
       return g.exec;
   hipGraph_t graph;
   SEM_HIP(hipStreamBeginCapture(b->s, hipStreamCaptureModeThreadLocal));
   try {
-    for (int q = 0; q < K; ++q) iteration(b, prec, jac, mode);
+    iterations(b, prec, K, jac, mode);
+    b->par = par;  // nothing has run yet
   } catch (...) {
+    b->par = par;
     hipGraph_t dummy;
     (void)hipStreamEndCapture(b->s, &dummy);
     throw;
@@ -1288,7 +1407,7 @@ static hipGraphExec_t get_graph(sem_batch *b, int prec, int K, int jac,
   hipGraphExec_t exec;
   SEM_HIP(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
   SEM_HIP(hipGraphDestroy(graph));
-  b->graphs.push_back({prec, K, jac, mode, ver, exec});
+  b->graphs.push_back({prec, K, jac, mode, par, ver, exec});
   return exec;
 }
 
@@ -1386,10 +1505,12 @@ static bool run_cg(sem_batch *b, int prec, int jac, const sem_solve_opts *o,
         }
     }
     if (mode == 0) maybe_compact(b);
-    if (o->use_graph)
+    if (o->use_graph) {
       SEM_HIP(hipGraphLaunch(get_graph(b, prec, K, jac, mode), b->s));
-    else
-      for (int q = 0; q < K; ++q) iteration(b, prec, jac, mode);
+      b->par ^= K & 1;
+    } else {
+      iterations(b, prec, K, jac, mode);
+    }
     if (b->snap_x != nullptr && b->snap_count < b->snap_max) {
       sem_handle *h = b->hs[0];
       const size_t bytes = (size_t)h->nG * sizeof(double);
@@ -1912,10 +2033,10 @@ void batch_tune(sem_batch *b, int prec, int *best_bs, int *best_gm,
     for (int gm : gms) {
       b->bs[prec] = bs;
       b->gmul[prec] = gm;
-      bax(b, prec, VP, VWL, 0);  // warm
+      bax(b, prec, VP, 0);  // warm
       SEM_HIP(hipEventRecord(b->ev0, b->s));
       const int reps = 3;
-      for (int r = 0; r < reps; ++r) bax(b, prec, VP, VWL, 0);
+      for (int r = 0; r < reps; ++r) bax(b, prec, VP, 0);
       SEM_HIP(hipEventRecord(b->ev1, b->s));
       SEM_HIP(hipEventSynchronize(b->ev1));
       float ms = 0;
