@@ -387,8 +387,8 @@ sem_status sem_mlp_set_params(sem_mlp *net, const float *params, int64_t n);
 /* Arithmetic of the section 4.2.2 correction network.  SEM_BF16 (default):
  * BF16 copies of the weights, BF16 hidden activations as layer inputs,
  * forward layers on the matrix cores with FP32 accumulation, backward in
- * FP32 on the same BF16 values.  SEM_FP32: FP32 weights and hidden
- * activations, forward and backward in FP32 on the vector units (for
+ * FP32 (FP32 matrix instructions) on the same BF16 values.  SEM_FP32: FP32
+ * weights and hidden activations, forward and backward in FP32 (for
  * element-by-element checks).  The input x is BF16 in both.  Any other p:
  * SEM_ERR_ARG.  Synchronises the device. */
 sem_status sem_mlp_set_precision(sem_mlp *net, int32_t p);

@@ -382,14 +382,8 @@ sem_status sem_mlp_loss_grad_factor(sem_mlp *net, const uint16_t *X,
   return guarded([&] {
     need(net != nullptr && X != nullptr && T != nullptr && B >= 1,
          "sem_mlp_loss_grad_factor: null argument or empty batch");
-    const double l = mlp_loss_grad_factor(net, X, ldx, T, K, B, true, strm(stream));
+    const double l = mlp_loss_grad_factor(net, X, ldx, T, K, B, grad, strm(stream));
     if (loss) *loss = l;
-    if (grad) {
-      int64_t np = 0;
-      mlp_info(net, nullptr, nullptr, nullptr, &np, nullptr);
-      SEM_HIP(hipMemcpyAsync(grad, mlp_grad_ptr(net), np * 4,
-                             hipMemcpyDeviceToDevice, strm(stream)));
-    }
   });
 }
 

@@ -1033,7 +1033,7 @@ void learn_train(sem_handle *h, sem_mlp *net, const double *const *bL, int nrhs,
                          Td.as<float>(), nt, Xb.as<uint16_t>(), Tb.as<float>());
       SEM_HIP(hipGetLastError());
       sum += mlp_loss_grad_factor(net, Xb.as<uint16_t>(), ldx, Tb.as<float>(), K,
-                                  B, true, s);
+                                  B, nullptr, s);
       mlp_adam(net, nullptr, o->lr, 0.9, 0.999, 1e-8, s);
       ++nb;
     }

@@ -8,8 +8,9 @@
 // Precision (per network): BF16 (the default) keeps FP32 master parameters
 // and BF16 copies of the weights that feed the forward layers, which run on
 // MFMA (v_mfma_f32_16x16x16_bf16, FP32 accumulation) with BF16 layer
-// inputs; the backward pass is FP32 on VALU using the same BF16-rounded
-// weights and layer inputs as the forward pass.  FP32 runs the forward
+// inputs; the backward pass is FP32 (v_mfma_f32_16x16x4_f32, full FP32
+// products and sums) on the same BF16-rounded weights and layer inputs as the
+// forward pass.  FP32 runs the forward
 // layers on VALU with the FP32 master weights and FP32 hidden activations
 // (the network input stays BF16), and the backward pass on the same values:
 // it differs from an exact evaluation only by FP32 rounding, which makes
@@ -17,8 +18,15 @@
 //
 // MFMA tile (16x16x16): lane l holds A[l % 16][4 (l / 16) + 0..3] and
 // B[4 (l / 16) + 0..3][l % 16] (4 BF16 values each); the result C[4 (l / 16) +
-// q][l % 16] is accumulator slot q.  A forward layer Y = X W^T gives every
-// wave a 16-row strip of X and all output columns.
+// q][l % 16] is accumulator slot q.
+//
+// A minibatch of training (512 samples, K = 27) is 0.2 GFLOP and 3 MB: what
+// bounds it is the latency of its chain of dependent kernels.  The chain is
+// forward (the three layers in one launch), loss, and one launch per layer of
+// the backward pass, whose weight, bias and input gradients depend on the
+// same data and run side by side: 68 us a pass, against 680 us with a launch
+// per product, a thread per bias (walking the batch) and a thread per sample
+// in the loss.
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -35,50 +43,95 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------
-// forward layer on MFMA
+// forward pass on MFMA
 // ---------------------------------------------------------------------------
-// Y = act(X W^T + b): X [M][ldx] BF16 (K columns used, K % 16 == 0),
-// W [16 NT][K] BF16 (rows >= N are zero), b [N] FP32.  Writes columns < N of
-// Yb (BF16, [M][ldyb]) and/or Yf (FP32, [M][ldyf]) when non-null.
-// Output columns are split over blockIdx.y in slices of 16 NT; W must have
-// at least 16 NT gridDim.y rows.
-template <int NT, bool RELU>
-__global__ void __launch_bounds__(256)
-    k_dense_mfma(int M, int K, int N, const uint16_t *__restrict__ X, int ldx,
-                 const uint16_t *__restrict__ W, const float *__restrict__ b,
-                 uint16_t *__restrict__ Yb, int ldyb, float *__restrict__ Yf,
-                 int ldyf) {
-  const int wave = threadIdx.x >> 6, l = threadIdx.x & 63;
-  const int row0 = (blockIdx.x * 4 + wave) * 16;
-  const int cbase = blockIdx.y * 16 * NT;
-  if (row0 >= M) return;  // whole wave; no barriers in this kernel
-  f32x4 acc[NT];
+// o = W3 relu(W2 relu(W1 x + b1) + b2) + b3 for the rows of X [M][ldx] BF16
+// (kin columns, kin % 16 == 0; W1 [128][kin], W2 [128][128], W3 [>= 16
+// ceil(n_out / 16)][128] BF16, the rows beyond n_out zero).  A workgroup takes 16 rows
+// through the three layers: wave w forms columns 16 w .. of both hidden
+// layers (passed on through LDS in BF16) and every eighth 16-column tile of
+// the output.  The weights of layer 2 and of the wave's first output tile are
+// asked for before anything else.  When non-null, h1b, h2b (BF16) and h1f,
+// h2f (FP32), all [M][128], receive the hidden activations for a backward
+// pass.
+constexpr int FW_WAVES = 8;
+__global__ void __launch_bounds__(64 * FW_WAVES)
+    k_forward_mfma(int M, int kin, int n_out, const uint16_t *__restrict__ X, int ldx,
+                   const uint16_t *__restrict__ W1, const float *__restrict__ b1,
+                   const uint16_t *__restrict__ W2, const float *__restrict__ b2,
+                   const uint16_t *__restrict__ W3, const float *__restrict__ b3,
+                   float *__restrict__ O, int ldo, uint16_t *__restrict__ h1b,
+                   uint16_t *__restrict__ h2b, float *__restrict__ h1f,
+                   float *__restrict__ h2f) {
+  constexpr int H = 128, PITCH = H + 8;  // rows 4 banks apart
+  __shared__ __align__(16) uint16_t lds[2][16 * PITCH];
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const int r = l & 15, g = l >> 4;
+  const int row0 = blockIdx.x * 16;
+  const int nt3 = (n_out + 15) / 16;
+  auto wfrag = [&](const uint16_t *W, int tile, int ks) {
+    return *reinterpret_cast<const s16x4 *>(W + (size_t)(16 * tile + r) * H + 16 * ks + 4 * g);
+  };
+  s16x4 w2[H / 16], w3[H / 16];
 #pragma unroll
-  for (int t = 0; t < NT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int ar = row0 + (l & 15);
-  const int kq = 4 * (l >> 4);
-  const bool arow = ar < M;
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    s16x4 a = {0, 0, 0, 0};
-    if (arow) a = *reinterpret_cast<const s16x4 *>(X + (size_t)ar * ldx + k0 + kq);
+  for (int ks = 0; ks < H / 16; ++ks) w2[ks] = wfrag(W2, w, ks);
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const s16x4 w = *reinterpret_cast<const s16x4 *>(
-          W + (size_t)(cbase + 16 * t + (l & 15)) * K + k0 + kq);
-      acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, w, acc[t], 0, 0, 0);
+  for (int ks = 0; ks < H / 16; ++ks) w3[ks] = wfrag(W3, w < nt3 ? w : 0, ks);
+  const int col = 16 * w + r;  // of the hidden layers
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  {
+    const int ar = row0 + r;
+    for (int k0 = 0; k0 < kin; k0 += 16) {
+      s16x4 a = {0, 0, 0, 0};
+      if (ar < M) a = *reinterpret_cast<const s16x4 *>(X + (size_t)ar * ldx + k0 + 4 * g);
+      const s16x4 b = *reinterpret_cast<const s16x4 *>(W1 + (size_t)col * kin + k0 + 4 * g);
+      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, acc, 0, 0, 0);
     }
   }
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int col = cbase + 16 * t + (l & 15);
+  // bias, relu; to LDS and, when wanted, to memory
+  auto hidden = [&](const f32x4 &v, float bias, uint16_t *L, uint16_t *hb, float *hf) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int row = row0 + 4 * (l >> 4) + q;
-      if (row < M && col < N) {
-        float v = acc[t][q] + b[col];
-        if (RELU) v = fmaxf(v, 0.0f);
-        if (Yb) Yb[(size_t)row * ldyb + col] = f32_to_bf16(v);
-        if (Yf) Yf[(size_t)row * ldyf + col] = v;
+      const int rr = 4 * g + q;
+      const float x = fmaxf(v[q] + bias, 0.0f);
+      const uint16_t xb = f32_to_bf16(x);
+      L[rr * PITCH + col] = xb;
+      if (row0 + rr < M) {
+        if (hb) hb[(size_t)(row0 + rr) * H + col] = xb;
+        if (hf) hf[(size_t)(row0 + rr) * H + col] = x;
+      }
+    }
+  };
+  hidden(acc, b1[col], lds[0], h1b, h1f);
+  __syncthreads();
+  acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int ks = 0; ks < H / 16; ++ks) {
+    const s16x4 a = *reinterpret_cast<const s16x4 *>(&lds[0][r * PITCH + 16 * ks + 4 * g]);
+    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, w2[ks], acc, 0, 0, 0);
+  }
+  hidden(acc, b2[col], lds[1], h2b, h2f);
+  __syncthreads();
+  s16x4 h[H / 16];
+#pragma unroll
+  for (int ks = 0; ks < H / 16; ++ks)
+    h[ks] = *reinterpret_cast<const s16x4 *>(&lds[1][r * PITCH + 16 * ks + 4 * g]);
+  for (int t = w; t < nt3; t += FW_WAVES) {
+    acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < H / 16; ++ks)
+      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(h[ks], w3[ks], acc, 0, 0, 0);
+    if (t + FW_WAVES < nt3) {  // the next tile's weights while this one is stored
+#pragma unroll
+      for (int ks = 0; ks < H / 16; ++ks) w3[ks] = wfrag(W3, t + FW_WAVES, ks);
+    }
+    const int c = 16 * t + r;
+    if (c < n_out) {
+      const float bias = b3[c];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int row = row0 + 4 * g + q;
+        if (row < M) O[(size_t)row * ldo + c] = acc[q] + bias;
       }
     }
   }
@@ -123,112 +176,227 @@ __global__ void __launch_bounds__(256)
 }
 
 // ---------------------------------------------------------------------------
-// backward kernels (FP32)
+// loss of the coarse-operator factor
 // ---------------------------------------------------------------------------
-
-// dW[n][k] = sum_b dY[b][n] X[b][k]  (n < N, k < Kv); dW row stride Kv
-template <class TX>
-__global__ void __launch_bounds__(256)
-    k_grad_w(int B, int N, int Kv, const float *__restrict__ dY, int lddy,
-             const TX *__restrict__ X, int ldx, float *__restrict__ dW) {
-  __shared__ float sy[16][17], sx[16][17];
-  const int tn = threadIdx.x / 16, tk = threadIdx.x % 16;
-  const int n = blockIdx.x * 16 + tn, k = blockIdx.y * 16 + tk;
-  float acc = 0.f;
-  for (int b0 = 0; b0 < B; b0 += 16) {
-    // load 16 samples: sy[bb][n-tile], sx[bb][k-tile]
-    const int bb = threadIdx.x / 16, c = threadIdx.x % 16;
-    const int bi = b0 + bb;
-    const int nn = blockIdx.x * 16 + c, kk = blockIdx.y * 16 + c;
-    sy[bb][c] = (bi < B && nn < N) ? dY[(size_t)bi * lddy + nn] : 0.f;
-    sx[bb][c] = (bi < B && kk < Kv) ? asf<TX>(X[(size_t)bi * ldx + kk]) : 0.f;
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 16; ++q) acc += sy[q][tn] * sx[q][tk];
-    __syncthreads();
-  }
-  if (n < N && k < Kv) dW[(size_t)n * Kv + k] = acc;
-}
-
-// db[n] = sum_b dY[b][n]
-__global__ void k_grad_b(int B, int N, const float *__restrict__ dY, int lddy,
-                         float *__restrict__ db) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= N) return;
-  float acc = 0.f;
-  for (int b = 0; b < B; ++b) acc += dY[(size_t)b * lddy + n];
-  db[n] = acc;
-}
-
-// dZ[b][k] = (sum_n dY[b][n] W[n][k]) * (H[b][k] > 0), W BF16 or FP32
-// [>=N][ldw]
-template <class TW>
-__global__ void __launch_bounds__(256)
-    k_grad_x(int B, int N, int K, const float *__restrict__ dY, int lddy,
-             const TW *__restrict__ W, int ldw,
-             const float *__restrict__ H, int ldh, float *__restrict__ dZ,
-             int lddz) {
-  __shared__ float sy[16][17], sw[16][17];
-  const int tb = threadIdx.x / 16, tk = threadIdx.x % 16;
-  const int b = blockIdx.x * 16 + tb, k = blockIdx.y * 16 + tk;
-  float acc = 0.f;
-  for (int n0 = 0; n0 < N; n0 += 16) {
-    const int r = threadIdx.x / 16, c = threadIdx.x % 16;
-    const int bi = blockIdx.x * 16 + r, ni = n0 + c;
-    sy[r][c] = (bi < B && ni < N) ? dY[(size_t)bi * lddy + ni] : 0.f;
-    const int nw = n0 + r, kw = blockIdx.y * 16 + c;
-    sw[r][c] = (nw < N && kw < K) ? asf<TW>(W[(size_t)nw * ldw + kw]) : 0.f;
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 16; ++q) acc += sy[tb][q] * sw[q][tk];
-    __syncthreads();
-  }
-  if (b < B && k < K)
-    dZ[(size_t)b * lddz + k] = H[(size_t)b * ldh + k] > 0.f ? acc : 0.f;
-}
-
-// coarse-operator factor: the output is a lower-triangular K x K factor L
-// (row-major packed); per sample, T holds y and alpha* (2K values) and the
-// loss is the mean of (L L^T y - alpha*)^2; dL = g v^T + y (L^T g)^T with
-// v = L^T y and g the loss gradient with respect to L L^T y.  One thread
-// per sample.
+// The output is a lower-triangular K x K factor L (row-major packed); per
+// sample, T holds y and alpha* (2K values) and the loss is the mean of
+// (L L^T y - alpha*)^2; dL = g v^T + y (L^T g)^T with v = L^T y and g the
+// loss gradient with respect to L L^T y.  One wave per sample, lane i the
+// row (column) i of the triangular products, the factor in LDS.
+constexpr int LF_WAVES = 4;
 template <int K>
-__global__ void __launch_bounds__(64)
+__global__ void __launch_bounds__(64 * LF_WAVES)
     k_loss_factor(int B, const float *__restrict__ O, int ldo,
                   const float *__restrict__ T, float *__restrict__ dO, int lddo,
                   double *__restrict__ lossp) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  const float *o = O + (size_t)b * ldo;
-  const float *y = T + (size_t)b * 2 * K, *as = y + K;
-  float v[K], g[K], w[K];
-  for (int j = 0; j < K; ++j) v[j] = w[j] = 0.f;
-  for (int i = 0, q = 0; i < K; ++i)
-    for (int j = 0; j <= i; ++j, ++q) v[j] += o[q] * y[i];
-  double loss = 0.0;
-  const float sc = (float)(2.0 / ((double)B * K));
-  for (int i = 0, q = 0; i < K; ++i) {
-    float a = 0.f;
-    for (int j = 0; j <= i; ++j) a += o[q + j] * v[j];
-    q += i + 1;
-    const float d = a - as[i];
-    loss += (double)d * (double)d;
-    g[i] = sc * d;
+  constexpr int KK = K * (K + 1) / 2;
+  struct Sample {
+    double dd[K];
+    float o[KK], y[K], v[K], g[K], w[K];
+  };
+  __shared__ Sample smp[LF_WAVES];
+  const int wv = threadIdx.x >> 6, l = threadIdx.x & 63;
+  const int b = blockIdx.x * LF_WAVES + wv;
+  if (b >= B) return;  // a whole wave; the waves do not wait for each other
+  Sample &S = smp[wv];
+  const float *o = O + (size_t)b * ldo, *t = T + (size_t)b * 2 * K;
+  for (int q = l; q < KK; q += 64) S.o[q] = o[q];
+  const int i = l < K ? l : K - 1;  // lanes beyond K repeat the last row
+  const float yi = t[i], as = t[K + i];
+  S.y[i] = yi;
+  wave_lds_sync();
+  const int row = i * (i + 1) / 2;
+  float v = 0.f;
+#pragma unroll
+  for (int m = 0; m < K; ++m)
+    if (m >= i) v += S.o[m * (m + 1) / 2 + i] * S.y[m];
+  S.v[i] = v;
+  wave_lds_sync();
+  float a = 0.f;
+#pragma unroll
+  for (int m = 0; m < K; ++m)
+    if (m <= i) a += S.o[row + m] * S.v[m];
+  const float d = a - as;
+  S.g[i] = (float)(2.0 / ((double)B * K)) * d;
+  S.dd[i] = (double)d * (double)d;
+  wave_lds_sync();
+  float w = 0.f;
+#pragma unroll
+  for (int m = 0; m < K; ++m)
+    if (m >= i) w += S.o[m * (m + 1) / 2 + i] * S.g[m];
+  S.w[i] = w;
+  wave_lds_sync();
+  for (int q = l; q < KK; q += 64) {
+    // packed index q = a (a + 1) / 2 + c
+    int ra = (int)((sqrtf(8.f * (float)q + 1.f) - 1.f) * 0.5f);
+    ra -= ra * (ra + 1) / 2 > q;
+    ra += (ra + 1) * (ra + 2) / 2 <= q;
+    const int c = q - ra * (ra + 1) / 2;
+    dO[(size_t)b * lddo + q] = S.g[ra] * S.v[c] + S.y[ra] * S.w[c];
   }
-  for (int i = 0, q = 0; i < K; ++i)
-    for (int j = 0; j <= i; ++j, ++q) w[j] += o[q] * g[i];
-  for (int i = 0, q = 0; i < K; ++i)
-    for (int j = 0; j <= i; ++j, ++q) dO[(size_t)b * lddo + q] = g[i] * v[j] + y[i] * w[j];
-  lossp[b] = loss;
+  double loss = 0.0;
+#pragma unroll
+  for (int m = 0; m < K; ++m) loss += S.dd[m];
+  if (l == 0) lossp[b] = loss;
 }
 
-__global__ void k_sum_losses(int B, const double *__restrict__ lossp, int nn,
-                             double *out) {
-  __shared__ double sm[4];
-  double a = 0.0;
-  for (int q = threadIdx.x; q < B; q += 256) a += lossp[q];
-  const double s = block_sum<256>(a, sm);
-  if (threadIdx.x == 0) out[0] = s / ((double)B * nn);
+// ---------------------------------------------------------------------------
+// backward pass of one layer (FP32 matrix instructions)
+// ---------------------------------------------------------------------------
+// v_mfma_f32_16x16x4_f32: lane l holds A[l % 16][l / 16] and
+// B[l / 16][l % 16]; the result C[4 (l / 16) + q][l % 16] is slot q.
+constexpr int BW_WAVES = 8;
+
+template <class TX, class TW> struct LayerGrad {
+  int B, N, K;                // samples, outputs, inputs of the layer
+  const float *dY;            // [B][lddy], the gradient at the layer's output
+  int lddy;
+  const TX *X;                // [B][ldx], the layer's input
+  int ldx;
+  float *dW, *db, *dW2, *db2; // gradients; *2: a second copy, or null
+  // the gradient at the input through its relu, K = 128 (null: none):
+  // dZ = (dY W) o (Hf > 0)
+  const TW *W;                // [N][128]
+  const float *Hf;            // [B][128]
+  float *dZ;                  // [B][128]
+  // mean loss (null: none)
+  const double *lossp;
+  double *loss;
+  double loss_count;
+  int tiles_w, tiles_x;       // workgroups per kind
+};
+
+// dW[n][k] = sum_b dY[b][n] X[b][k] for 16 n and 32 k, the samples dealt to
+// the eight waves four at a time and their sums added in wave order; the
+// first k tile also sums dY itself (db), as one more column of ones
+template <class TX, class TW>
+__device__ inline void grad_w_tile(const LayerGrad<TX, TW> &p, int tile, float *red) {
+  const int nk = (p.K + 31) / 32;
+  const int n0 = tile / nk * 16, k0 = tile % nk * 32;
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63, r = l & 15, g = l >> 4;
+  const bool n_ok = n0 + r < p.N, k_ok0 = k0 + r < p.K, k_ok1 = k0 + 16 + r < p.K;
+  f32x4 c0 = {0.f, 0.f, 0.f, 0.f}, c1 = c0, cb = c0;
+  constexpr int U = 8;
+  for (int b0 = 4 * w; b0 < p.B; b0 += 4 * BW_WAVES * U) {
+    float a[U], x0[U], x1[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int b = b0 + 4 * BW_WAVES * u + g;
+      const bool ok = b < p.B;
+      a[u] = ok && n_ok ? p.dY[(size_t)b * p.lddy + n0 + r] : 0.f;
+      x0[u] = ok && k_ok0 ? asf<TX>(p.X[(size_t)b * p.ldx + k0 + r]) : 0.f;
+      x1[u] = ok && k_ok1 ? asf<TX>(p.X[(size_t)b * p.ldx + k0 + 16 + r]) : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      c0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], x0[u], c0, 0, 0, 0);
+      c1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], x1[u], c1, 0, 0, 0);
+      if (k0 == 0) cb = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u], 1.f, cb, 0, 0, 0);
+    }
+  }
+  // red[wave][3][16 rows][16 columns]
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int at = w * 768 + (4 * g + q) * 16 + r;
+    red[at] = c0[q];
+    red[at + 256] = c1[q];
+    red[at + 512] = cb[q];
+  }
+  __syncthreads();
+  const int t = threadIdx.x;  // 512 threads: tile t / 256, row, column
+  const int n = n0 + (t & 255) / 16, k = k0 + (t / 256) * 16 + (t & 15);
+  float s = 0.f;
+#pragma unroll
+  for (int q = 0; q < BW_WAVES; ++q) s += red[q * 768 + t];
+  if (n < p.N && k < p.K) {
+    p.dW[(size_t)n * p.K + k] = s;
+    if (p.dW2) p.dW2[(size_t)n * p.K + k] = s;
+  }
+  if (k0 == 0 && t < 16 && n0 + t < p.N) {
+    float sb = 0.f;
+#pragma unroll
+    for (int q = 0; q < BW_WAVES; ++q) sb += red[q * 768 + 512 + t * 16];
+    p.db[n0 + t] = sb;
+    if (p.db2) p.db2[n0 + t] = sb;
+  }
+}
+
+// four consecutive values of a row of weights
+__device__ inline void load4(const float *p, float (&v)[4]) {
+  // (a layer's rows of parameters are only 4-byte aligned)
+#pragma unroll
+  for (int j = 0; j < 4; ++j) v[j] = p[j];
+}
+__device__ inline void load4(const uint16_t *p, float (&v)[4]) {
+  const s16x4 x = *reinterpret_cast<const s16x4 *>(p);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) v[j] = bf16_to_f32((uint16_t)x[j]);
+}
+
+// dZ[b][k] = (sum_n dY[b][n] W[n][k]) (Hf[b][k] > 0) for 16 b.  Wave w takes
+// the columns 64 (w % 2) .. + 63 and every fourth chunk of 16 outputs n
+// (w / 2 first); the four partial sums are added in order.  Within a chunk,
+// slot q of lane group g takes n = 4 g + q and tile j the columns 4 r + j,
+// so that a lane reads consecutive entries of its row of dY and of W (one
+// column a load and every wave reading all of dY: 24 us against 12 at 512 x 378).
+template <class TX, class TW>
+__device__ inline void grad_x_tile(const LayerGrad<TX, TW> &p, int tile, float *red) {
+  constexpr int H = 128;
+  const int w = threadIdx.x >> 6, l = threadIdx.x & 63, r = l & 15, g = l >> 4;
+  const int b = tile * 16 + r, k0 = 64 * (w & 1) + 4 * r;
+  f32x4 c[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) c[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int n0 = 16 * (w >> 1); n0 < p.N; n0 += 64) {
+    float a[4], x[4][4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int n = n0 + 4 * g + q;
+      a[q] = n < p.N && b < p.B ? p.dY[(size_t)b * p.lddy + n] : 0.f;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) x[q][j] = 0.f;
+      if (n < p.N) load4(p.W + (size_t)n * H + k0, x[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        c[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q], x[q][j], c[j], 0, 0, 0);
+  }
+  // red[quarter][row][column]
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) red[(w >> 1) * 2048 + (4 * g + q) * H + k0 + j] = c[j][q];
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int t = u * 64 * BW_WAVES + threadIdx.x, row = tile * 16 + t / H;
+    if (row < p.B) {
+      const size_t at = (size_t)row * H + t % H;
+      const float s = ((red[t] + red[2048 + t]) + red[4096 + t]) + red[6144 + t];
+      p.dZ[at] = p.Hf[at] > 0.f ? s : 0.f;
+    }
+  }
+}
+
+// workgroups [0, tiles_x) form dZ, the next tiles_w the weight gradients, one
+// more (when asked for) the mean loss
+template <class TX, class TW>
+__global__ void __launch_bounds__(64 * BW_WAVES) k_layer_grad(LayerGrad<TX, TW> p) {
+  __shared__ float red[4 * 2048];  // >= BW_WAVES * 768
+  __shared__ double sm[BW_WAVES];
+  const int q = blockIdx.x;
+  if (q < p.tiles_x) {
+    grad_x_tile(p, q, red);
+  } else if (q < p.tiles_x + p.tiles_w) {
+    grad_w_tile(p, q - p.tiles_x, red);
+  } else {
+    double a = 0.0;
+    for (int m = threadIdx.x; m < p.B; m += 64 * BW_WAVES) a += p.lossp[m];
+    const double s = block_sum<64 * BW_WAVES>(a, sm);
+    if (threadIdx.x == 0) *p.loss = s / p.loss_count;
+  }
 }
 
 __global__ void k_adam(int64_t n, float *__restrict__ th, float *__restrict__ m,
@@ -276,7 +444,7 @@ __global__ void k_refresh(int n_in, int kin, int H, int n_out, int w3rows,
 struct sem_mlp {
   int n_in = 0, H = 0, n_out = 0, kin = 0;
   int prec = SEM_BF16;      // SEM_BF16 (MFMA, BF16 weights) or SEM_FP32 (VALU)
-  int nt3 = 1, gy3 = 1, w3rows = 16;  // output layer: tiles per wave, grid.y
+  int w3rows = 16;          // rows of W3b: n_out, padded
   int64_t np = 0, step = 0;
   uint64_t version = 1;     // changes whenever the parameters change
   double damping = 1.0;     // scale of the correction in the preconditioner
@@ -287,8 +455,8 @@ struct sem_mlp {
                             // kernels (captured graphs see its updates)
   // training scratch, sized for `cap` samples
   int cap = 0;
-  sem::DevBuf h1b, h2b, h1f, h2f, of, dO, dz2, dz1, lossp, lossd;
-  double *host_loss = nullptr;
+  sem::DevBuf h1b, h2b, h1f, h2f, of, dO, dz2, dz1, lossp;
+  double *host_loss = nullptr;  // pinned; the loss kernel writes it
   ~sem_mlp() {
     if (host_loss) (void)hipHostFree(host_loss);
   }
@@ -323,15 +491,7 @@ sem_mlp *mlp_create(int n_in, int H, int n_out, uint64_t seed) {
     net->H = H;
     net->n_out = n_out;
     net->kin = (n_in + 15) / 16 * 16;
-    if (n_out <= 16) {
-      net->nt3 = 1;
-      net->gy3 = 1;
-      net->w3rows = 16;
-    } else {
-      net->nt3 = 8;
-      net->gy3 = (n_out + 127) / 128;
-      net->w3rows = 128 * net->gy3;
-    }
+    net->w3rows = (n_out + 15) / 16 * 16;
     net->np = mlp_np(n_in, H, n_out);
     net->th.alloc(net->np * 4);
     net->m.alloc(net->np * 4);
@@ -398,18 +558,17 @@ static void ensure_scratch(sem_mlp *net, int B) {
   net->dz2.alloc((size_t)B * H * 4);
   net->dz1.alloc((size_t)B * H * 4);
   net->lossp.alloc((size_t)B * 8);
-  net->lossd.alloc(8);
   net->cap = B;
 }
 
 // forward of B samples X [B][ldx] BF16 (ldx >= kin, padding columns zero)
-// into O [B][ldo] FP32 with the hidden activations in the given buffers:
-// BF16 precision writes h1b, h2b (BF16 [B][H], the next layer's inputs) and,
-// when non-null, their FP32 values h1f, h2f (for a backward pass); FP32
-// precision writes h1f, h2f (FP32 [B][H]) only.
-static void forward_into(sem_mlp *net, const uint16_t *X, int ldx, int B,
-                         float *O, int ldo, uint16_t *h1b, uint16_t *h2b,
-                         float *h1f, float *h2f, hipStream_t s) {
+// into O [B][ldo] FP32.  FP32 precision uses the FP32 scratch; keep: the
+// hidden activations stay in the network's scratch for a backward pass (BF16
+// precision: h1b, h2b, the next layer's inputs, and their FP32 values h1f,
+// h2f)
+static void forward_into(sem_mlp *net, const uint16_t *X, int ldx, int B, float *O, int ldo,
+                         bool keep, hipStream_t s) {
+  if (B <= 0) return;
   if (ldx < net->kin || ldx % 16 != 0)
     fail(SEM_ERR_ARG, "mlp_forward: ldx must be >= padded n_in and a multiple of 16");
   const int H = net->H;
@@ -419,8 +578,10 @@ static void forward_into(sem_mlp *net, const uint16_t *X, int ldx, int B,
   const float *b2 = W2 + (int64_t)H * H;
   const float *W3 = b2 + H;
   const float *b3 = W3 + (int64_t)net->n_out * H;
+  if (keep || net->prec == SEM_FP32) ensure_scratch(net, B);
+  const unsigned gm = (unsigned)((B + 15) / 16);
   if (net->prec == SEM_FP32) {
-    const unsigned gm = (unsigned)((B + 15) / 16);
+    float *h1f = net->h1f.as<float>(), *h2f = net->h2f.as<float>();
     hipLaunchKernelGGL((k_dense_f32<uint16_t, true>), dim3(gm, H / 16), dim3(256),
                        0, s, B, net->n_in, H, X, ldx, W1, net->n_in, b1, h1f, H);
     hipLaunchKernelGGL((k_dense_f32<float, true>), dim3(gm, H / 16), dim3(256), 0,
@@ -432,114 +593,90 @@ static void forward_into(sem_mlp *net, const uint16_t *X, int ldx, int B,
     SEM_HIP(hipGetLastError());
     return;
   }
-  const unsigned grid = (unsigned)((B + 63) / 64);
-  hipLaunchKernelGGL((k_dense_mfma<8, true>), dim3(grid), dim3(256), 0, s, B,
-                     net->kin, H, X, ldx, net->W1b.as<uint16_t>(), b1, h1b, H,
-                     h1f, H);
-  hipLaunchKernelGGL((k_dense_mfma<8, true>), dim3(grid), dim3(256), 0, s, B, H,
-                     H, h1b, H, net->W2b.as<uint16_t>(), b2, h2b, H, h2f, H);
-  if (net->nt3 == 1)
-    hipLaunchKernelGGL((k_dense_mfma<1, false>), dim3(grid), dim3(256), 0, s, B, H,
-                       net->n_out, h2b, H, net->W3b.as<uint16_t>(), b3,
-                       (uint16_t *)nullptr, 0, O, ldo);
-  else
-    hipLaunchKernelGGL((k_dense_mfma<8, false>), dim3(grid, net->gy3), dim3(256), 0,
-                       s, B, H, net->n_out, h2b, H, net->W3b.as<uint16_t>(), b3,
-                       (uint16_t *)nullptr, 0, O, ldo);
+  hipLaunchKernelGGL(k_forward_mfma, dim3(gm), dim3(64 * FW_WAVES), 0, s, B, net->kin,
+                     net->n_out, X, ldx, net->W1b.as<uint16_t>(), b1,
+                     net->W2b.as<uint16_t>(), b2, net->W3b.as<uint16_t>(), b3, O, ldo,
+                     keep ? net->h1b.as<uint16_t>() : nullptr,
+                     keep ? net->h2b.as<uint16_t>() : nullptr,
+                     keep ? net->h1f.as<float>() : nullptr,
+                     keep ? net->h2f.as<float>() : nullptr);
   SEM_HIP(hipGetLastError());
 }
 
-// forward with the hidden activations kept in the network's scratch (grown
-// to B samples when needed) for a backward pass
 void mlp_forward(sem_mlp *net, const uint16_t *X, int ldx, int B, float *O,
                  int ldo, hipStream_t s) {
-  if (B <= 0) return;
-  ensure_scratch(net, B);
-  forward_into(net, X, ldx, B, O, ldo, net->h1b.as<uint16_t>(),
-               net->h2b.as<uint16_t>(), net->h1f.as<float>(), net->h2f.as<float>(),
-               s);
+  forward_into(net, X, ldx, B, O, ldo, false, s);
 }
 
-// backward pass from net->dO (written by a loss kernel) into net->grad
-// (flat parameter order), on the weights and layer inputs the forward pass
-// used; then the mean loss over B samples of `count` terms each
-static double mlp_backward(sem_mlp *net, const uint16_t *X, int ldx, int B,
-                           int count, bool host_loss, hipStream_t s) {
+// Backward pass from net->dO (written by a loss kernel) into net->grad
+// (flat parameter order) and, when non-null, grad, on the weights and layer
+// inputs the forward pass used; returns the mean loss over B samples of
+// `count` terms each.  TH: the type of the hidden layers' values and of the
+// weights in the products (BF16, or FP32 for an FP32 network).
+template <class TH>
+static double mlp_backward(sem_mlp *net, const uint16_t *X, int ldx, int B, int count,
+                           float *grad, hipStream_t s) {
+  constexpr bool f32 = sizeof(TH) == 4;
   const int H = net->H;
   const int wo = net->n_out > 16 ? net->n_out : 16;
-  const bool f32 = net->prec == SEM_FP32;
+  const int64_t o1 = 0, ob1 = o1 + (int64_t)H * net->n_in, o2 = ob1 + H,
+                ob2 = o2 + (int64_t)H * H, o3 = ob2 + H, ob3 = o3 + (int64_t)net->n_out * H;
   float *g = net->grad.as<float>();
-  float *gW1 = g, *gb1 = gW1 + (int64_t)H * net->n_in, *gW2 = gb1 + H,
-        *gb2 = gW2 + (int64_t)H * H, *gW3 = gb2 + H,
-        *gb3 = gW3 + (int64_t)net->n_out * H;
-  const float *W2 = net->th.as<float>() + (int64_t)H * net->n_in + H;
-  const float *W3 = W2 + (int64_t)H * H + H;
-  const float *dO = net->dO.as<float>(), *dz2 = net->dz2.as<float>(),
-              *dz1 = net->dz1.as<float>();
-  const float *h1f = net->h1f.as<float>(), *h2f = net->h2f.as<float>();
-  // layer 3
-  if (f32)
-    hipLaunchKernelGGL((k_grad_w<float>), dim3((net->n_out + 15) / 16, H / 16),
-                       dim3(256), 0, s, B, net->n_out, H, dO, wo, h2f, H, gW3);
-  else
-    hipLaunchKernelGGL((k_grad_w<uint16_t>), dim3((net->n_out + 15) / 16, H / 16),
-                       dim3(256), 0, s, B, net->n_out, H, dO, wo,
-                       (const uint16_t *)net->h2b.as<uint16_t>(), H, gW3);
-  hipLaunchKernelGGL(k_grad_b, dim3((net->n_out + 127) / 128), dim3(128), 0, s, B,
-                     net->n_out, dO, wo, gb3);
-  if (f32)
-    hipLaunchKernelGGL((k_grad_x<float>), dim3((B + 15) / 16, H / 16), dim3(256), 0,
-                       s, B, net->n_out, H, dO, wo, W3, H, h2f, H,
-                       net->dz2.as<float>(), H);
-  else
-    hipLaunchKernelGGL((k_grad_x<uint16_t>), dim3((B + 15) / 16, H / 16),
-                       dim3(256), 0, s, B, net->n_out, H, dO, wo,
-                       (const uint16_t *)net->W3b.as<uint16_t>(), H, h2f, H,
-                       net->dz2.as<float>(), H);
-  // layer 2
-  if (f32)
-    hipLaunchKernelGGL((k_grad_w<float>), dim3(H / 16, H / 16), dim3(256), 0, s, B,
-                       H, H, dz2, H, h1f, H, gW2);
-  else
-    hipLaunchKernelGGL((k_grad_w<uint16_t>), dim3(H / 16, H / 16), dim3(256), 0, s,
-                       B, H, H, dz2, H, (const uint16_t *)net->h1b.as<uint16_t>(),
-                       H, gW2);
-  hipLaunchKernelGGL(k_grad_b, dim3(1), dim3(128), 0, s, B, H, dz2, H, gb2);
-  if (f32)
-    hipLaunchKernelGGL((k_grad_x<float>), dim3((B + 15) / 16, H / 16), dim3(256), 0,
-                       s, B, H, H, dz2, H, W2, H, h1f, H, net->dz1.as<float>(), H);
-  else
-    hipLaunchKernelGGL((k_grad_x<uint16_t>), dim3((B + 15) / 16, H / 16),
-                       dim3(256), 0, s, B, H, H, dz2, H,
-                       (const uint16_t *)net->W2b.as<uint16_t>(), H, h1f, H,
-                       net->dz1.as<float>(), H);
+  const float *th = net->th.as<float>();
+  const TH *W2 = f32 ? (const TH *)(th + o2) : (const TH *)net->W2b.p;
+  const TH *W3 = f32 ? (const TH *)(th + o3) : (const TH *)net->W3b.p;
+  const TH *h1 = f32 ? (const TH *)net->h1f.p : (const TH *)net->h1b.p;
+  const TH *h2 = f32 ? (const TH *)net->h2f.p : (const TH *)net->h2b.p;
+  auto second = [&](int64_t off) { return grad ? grad + off : nullptr; };
+  auto launch = [&](auto p) {
+    p.B = B;
+    p.tiles_w = (p.N + 15) / 16 * ((p.K + 31) / 32);
+    p.tiles_x = p.dZ ? (B + 15) / 16 : 0;
+    const int grid = p.tiles_x + p.tiles_w + (p.loss ? 1 : 0);
+    void (*kernel)(decltype(p)) = k_layer_grad;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * BW_WAVES), 0, s, p);
+  };
+  LayerGrad<TH, TH> p3{};
+  p3.N = net->n_out, p3.K = H;
+  p3.dY = net->dO.as<float>(), p3.lddy = wo;
+  p3.X = h2, p3.ldx = H;
+  p3.dW = g + o3, p3.db = g + ob3, p3.dW2 = second(o3), p3.db2 = second(ob3);
+  p3.W = W3, p3.Hf = net->h2f.as<float>(), p3.dZ = net->dz2.as<float>();
+  p3.lossp = net->lossp.as<double>(), p3.loss = net->host_loss;
+  p3.loss_count = (double)B * count;
+  launch(p3);
+  LayerGrad<TH, TH> p2{};
+  p2.N = H, p2.K = H;
+  p2.dY = net->dz2.as<float>(), p2.lddy = H;
+  p2.X = h1, p2.ldx = H;
+  p2.dW = g + o2, p2.db = g + ob2, p2.dW2 = second(o2), p2.db2 = second(ob2);
+  p2.W = W2, p2.Hf = net->h1f.as<float>(), p2.dZ = net->dz1.as<float>();
+  launch(p2);
   // layer 1 (the input X is BF16 in both precisions)
-  hipLaunchKernelGGL((k_grad_w<uint16_t>),
-                     dim3(H / 16, (net->n_in + 15) / 16), dim3(256), 0, s, B, H,
-                     net->n_in, dz1, H, X, ldx, gW1);
-  hipLaunchKernelGGL(k_grad_b, dim3(1), dim3(128), 0, s, B, H, dz1, H, gb1);
-  hipLaunchKernelGGL(k_sum_losses, dim3(1), dim3(256), 0, s, B,
-                     net->lossp.as<double>(), count, net->lossd.as<double>());
+  LayerGrad<uint16_t, TH> p1{};
+  p1.N = H, p1.K = net->n_in;
+  p1.dY = net->dz1.as<float>(), p1.lddy = H;
+  p1.X = X, p1.ldx = ldx;
+  p1.dW = g + o1, p1.db = g + ob1, p1.dW2 = second(o1), p1.db2 = second(ob1);
+  launch(p1);
   SEM_HIP(hipGetLastError());
-  if (!host_loss) return 0.0;
-  SEM_HIP(hipMemcpyAsync(net->host_loss, net->lossd.p, sizeof(double),
-                         hipMemcpyDeviceToHost, s));
   SEM_HIP(hipStreamSynchronize(s));
   return *net->host_loss;
 }
 
 // loss and gradient of the coarse-operator factor (n_out = K(K+1)/2,
-// K in {1, 8, 27}); T [B][2K] holds y and alpha* per sample
+// K in {1, 8, 27}); T [B][2K] holds y and alpha* per sample.  The gradient
+// goes to the network's own buffer and, when non-null, to grad.
 double mlp_loss_grad_factor(sem_mlp *net, const uint16_t *X, int ldx,
-                            const float *T, int K, int B, bool host_loss,
+                            const float *T, int K, int B, float *grad,
                             hipStream_t s) {
   if (net->n_out != K * (K + 1) / 2 || (K != 1 && K != 8 && K != 27))
     fail(SEM_ERR_ARG, "mlp_loss_grad_factor: K must be 1, 8 or 27 and "
                       "n_out = K(K+1)/2");
   ensure_scratch(net, B);
   const int wo = net->n_out > 16 ? net->n_out : 16;
-  mlp_forward(net, X, ldx, B, net->of.as<float>(), wo, s);
-  const dim3 g((unsigned)((B + 63) / 64)), t(64);
+  forward_into(net, X, ldx, B, net->of.as<float>(), wo, true, s);
+  const dim3 g((unsigned)((B + LF_WAVES - 1) / LF_WAVES)), t(64 * LF_WAVES);
   if (K == 1)
     hipLaunchKernelGGL(k_loss_factor<1>, g, t, 0, s, B, net->of.as<float>(), wo, T,
                        net->dO.as<float>(), wo, net->lossp.as<double>());
@@ -549,7 +686,9 @@ double mlp_loss_grad_factor(sem_mlp *net, const uint16_t *X, int ldx,
   else
     hipLaunchKernelGGL(k_loss_factor<27>, g, t, 0, s, B, net->of.as<float>(), wo, T,
                        net->dO.as<float>(), wo, net->lossp.as<double>());
-  return mlp_backward(net, X, ldx, B, K, host_loss, s);
+  SEM_HIP(hipGetLastError());
+  return net->prec == SEM_FP32 ? mlp_backward<float>(net, X, ldx, B, K, grad, s)
+                               : mlp_backward<uint16_t>(net, X, ldx, B, K, grad, s);
 }
 
 uint64_t mlp_version(const sem_mlp *net) { return net->version; }
@@ -683,8 +822,6 @@ void mlp_info(const sem_mlp *net, int *n_in, int *H, int *n_out, int64_t *np,
 }
 
 int mlp_padded_inputs(const sem_mlp *net) { return net->kin; }
-
-const float *mlp_grad_ptr(const sem_mlp *net) { return net->grad.as<float>(); }
 
 double mlp_damping(const sem_mlp *net) { return net->damping; }
 double mlp_ref_rate(const sem_mlp *net) { return net->ref_rate; }

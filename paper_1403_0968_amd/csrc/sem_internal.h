@@ -262,14 +262,13 @@ void mlp_forward(sem_mlp *net, const uint16_t *X, int ldx, int B, float *O,
 void mlp_set_precision(sem_mlp *net, int prec);
 int mlp_precision(const sem_mlp *net);
 double mlp_loss_grad_factor(sem_mlp *net, const uint16_t *X, int ldx,
-                            const float *T, int K, int B, bool host_loss,
+                            const float *T, int K, int B, float *grad,
                             hipStream_t s);
 uint64_t mlp_version(const sem_mlp *net);
 void mlp_adam(sem_mlp *net, const float *grad, double lr, double b1, double b2,
               double eps, hipStream_t s);
 void mlp_save(const sem_mlp *net, const char *path);
 sem_mlp *mlp_load(const char *path);
-const float *mlp_grad_ptr(const sem_mlp *net);
 double mlp_damping(const sem_mlp *net);
 double mlp_ref_rate(const sem_mlp *net);
 void mlp_set_damping(sem_mlp *net, double damping, double ref_rate);
