@@ -12,9 +12,9 @@
 //     different banks);
 //   * all loads of an element (its u column and the 6 n1 geometric factors of
 //     the column) are issued before any arithmetic, so each wave keeps its
-//     whole input in flight; the factors are read once per operator
-//     application and bypass the caches (non-temporal loads), and so do the
-//     outputs of the standalone operator;
+//     whole input in flight; factors and outputs of operators beyond the
+//     last-level cache bypass the caches where whole lines are loaded
+//     (OpShape);
 //   * u, the r-flux and the s-flux each have their own LDS array.
 // Storage/compute type combinations:
 //   FP64: u, G, w double; FP32: float everywhere;
@@ -42,31 +42,47 @@ namespace sem {
 // ---------------------------------------------------------------------------
 // standalone operator: one tile per workgroup
 // ---------------------------------------------------------------------------
-template <int N1, class TU, class TG, class TW, class TC, bool MASS>
-__global__ void __launch_bounds__((OpShape<N1, sizeof(TC)>::THREADS))
+template <int N1, class TU, class TG, class TW, class TC, bool MASS, int REG>
+__global__ void __launch_bounds__((OpShape<N1, sizeof(TG), false, REG>::THREADS))
     k_ax(int64_t E, const TC *__restrict__ D, const TG *__restrict__ G,
          const TU *__restrict__ u, TW *__restrict__ w, const TG *__restrict__ H) {
-  using S = OpShape<N1, sizeof(TC)>;
+  using S = OpShape<N1, sizeof(TG), false, REG>;
   __shared__ __align__(16) TC smem[lds_words<N1, TC>(S::EPB)];
-  ax_tile<N1, S::EPB, TU, TG, TW, TC, false, true, MASS, S::NTG, false, S::PRED>(
+  ax_tile<N1, S::EPB, TU, TG, TW, TC, false, REG == AX_STREAM, MASS, S::NTG, false, S::PRED>(
       threadIdx.x, (int64_t)blockIdx.x * S::EPB, E, D, G, u, w, nullptr, smem, H);
+}
+
+template <int N1, class TU, class TG, class TW, class TC, bool MASS, int REG>
+static void launch_reg(int64_t E, const void *D, const void *G, const void *H,
+                       const void *u, void *w, hipStream_t s) {
+  using S = OpShape<N1, sizeof(TG), false, REG>;
+  const int64_t blocks = (E + S::EPB - 1) / S::EPB;
+  if (blocks == 0) return;
+  hipLaunchKernelGGL((k_ax<N1, TU, TG, TW, TC, MASS, REG>), dim3((unsigned)blocks),
+                     dim3(S::THREADS), 0, s, E, (const TC *)D, (const TG *)G,
+                     (const TU *)u, (TW *)w, (const TG *)H);
+}
+
+template <int N1, class TU, class TG, class TW, class TC, bool MASS>
+static void launch_mass(int64_t E, const void *D, const void *G, const void *H,
+                        const void *u, void *w, hipStream_t s) {
+  const AxRegime reg =
+      ax_regime(E * N1 * N1 * N1, (int)(6 * sizeof(TG) + sizeof(TU) + sizeof(TW)));
+  if (reg == AX_SMALL)
+    launch_reg<N1, TU, TG, TW, TC, MASS, AX_SMALL>(E, D, G, H, u, w, s);
+  else if (reg == AX_CACHED)
+    launch_reg<N1, TU, TG, TW, TC, MASS, AX_CACHED>(E, D, G, H, u, w, s);
+  else
+    launch_reg<N1, TU, TG, TW, TC, MASS, AX_STREAM>(E, D, G, H, u, w, s);
 }
 
 template <int N1, class TU, class TG, class TW, class TC>
 static void launch_nt(int64_t E, const void *D, const void *G, const void *H,
                       const void *u, void *w, hipStream_t s) {
-  using S = OpShape<N1, sizeof(TC)>;
-  const int64_t blocks = (E + S::EPB - 1) / S::EPB;
-  if (blocks == 0) return;
-  const dim3 grid((unsigned)blocks), block(S::THREADS);
   if (H != nullptr)
-    hipLaunchKernelGGL((k_ax<N1, TU, TG, TW, TC, true>), grid, block, 0, s, E,
-                       (const TC *)D, (const TG *)G, (const TU *)u, (TW *)w,
-                       (const TG *)H);
+    launch_mass<N1, TU, TG, TW, TC, true>(E, D, G, H, u, w, s);
   else
-    hipLaunchKernelGGL((k_ax<N1, TU, TG, TW, TC, false>), grid, block, 0, s, E,
-                       (const TC *)D, (const TG *)G, (const TU *)u, (TW *)w,
-                       (const TG *)nullptr);
+    launch_mass<N1, TU, TG, TW, TC, false>(E, D, G, H, u, w, s);
 }
 
 template <int N1>
@@ -115,7 +131,7 @@ __device__ inline DirArgs<TV> batch_dir(const BatchSolve &sd, CgState *st, const
           bd.vbeg[s],          bd.vbeg[s + 1]};
 }
 
-template <int BS, class TV, class TG, class TC, int DIR, int N1>
+template <int BS, class TV, class TG, class TC, int DIR, bool STREAM, int N1>
 __device__ __forceinline__ void bax_one(const BatchSolve &sd, int64_t e0, int src,
                                         const DirArgs<TV> &dir, TC *smem) {
   const TV *u = (const TV *)(sizeof(TV) == 8 ? sd.v64[src] : sd.v32[src]);
@@ -124,21 +140,32 @@ __device__ __forceinline__ void bax_one(const BatchSolve &sd, int64_t e0, int sr
                              : sizeof(TG) == 4 ? sd.G32
                                                : sd.G16);
   const TC *D = (const TC *)(sizeof(TC) == 8 ? sd.D64 : sd.D32);
-  // the output streams non-temporally (a batch's E-vectors together are far
-  // larger than the caches: 256 solves 6.98 -> 6.85 s)
-  ax_tile<N1, BTile<BS, N1>::EPB, TV, TG, TV, TC, true, true, false, true, DIR != 0, false, DIR>(
+  // hints as the single-solve operator's; with the vectors beyond the cache
+  // the output streams non-temporally
+  constexpr bool NTG = OpShape<N1, sizeof(TG), true, STREAM ? AX_STREAM : AX_CACHED>::NTG;
+  ax_tile<N1, BTile<BS, N1>::EPB, TV, TG, TV, TC, true, DIR == 3 || (DIR == 0 && STREAM), false, NTG,
+          DIR != 0, false, DIR, true>(
       threadIdx.x, e0, sd.E, D, G, u, w, &sd.box, smem, nullptr, DIR ? sd.edot : nullptr,
       DIR == 1 || DIR == 2 ? &dir : nullptr);
 }
 
-template <int BS, class TV, class TG, class TC, int DIR, int... N1s>
+template <int BS, class TV, class TG, class TC, int DIR, bool STREAM, int... N1s>
 __global__ void __launch_bounds__(BS)
     k_bax(const BatchSolve *__restrict__ sds, CgState *st,
           const AxItem *__restrict__ items, int nitems, int src, BaxDir bd) {
   extern __shared__ __align__(16) unsigned char dyn_smem[];
   TC *smem = reinterpret_cast<TC *>(dyn_smem);
-  for (int q = blockIdx.x; q < nitems; q += gridDim.x) {
-    const AxItem it = items[q];
+  // a workgroup walks a run of consecutive items, and the workgroups of an
+  // XCD take consecutive runs: their elements share nodes of the gathered
+  // vector.  The next item is asked for before the current one's work, so
+  // that its latency is hidden
+  const int run = (nitems + (int)gridDim.x - 1) / (int)gridDim.x;
+  const int q0 = (int)xcd_run_block(blockIdx.x, gridDim.x) * run;
+  const int q1 = min(q0 + run, nitems);
+  AxItem next = q0 < q1 ? items[q0] : AxItem{};
+  for (int q = q0; q < q1; ++q) {
+    const AxItem it = next;
+    if (q + 1 < q1) next = items[q + 1];
     const BatchSolve &sd = sds[it.solve];
     DirArgs<TV> dir = {};
     if constexpr (DIR == 1 || DIR == 2) dir = batch_dir<TV>(sd, st, bd, it.solve);
@@ -148,7 +175,7 @@ __global__ void __launch_bounds__(BS)
       continue;  // uniform per block
     const int n1 = sd.N1;
     // exactly one of the compiled orders matches the item's order
-    ((n1 == N1s ? bax_one<BS, TV, TG, TC, DIR, N1s>(sd, it.elem0, src, dir, smem)
+    ((n1 == N1s ? bax_one<BS, TV, TG, TC, DIR, STREAM, N1s>(sd, it.elem0, src, dir, smem)
                 : void()),
      ...);
     __syncthreads();  // the next item may use another LDS layout
@@ -164,16 +191,16 @@ template <int BS, class TC, int... N1s> constexpr int max_lds_words() {
   return m;
 }
 
-template <int BS, class TV, class TG, class TC, int DIR, int... N1s>
+template <int BS, class TV, class TG, class TC, int DIR, bool STREAM, int... N1s>
 static void launch_bax_set(const BatchSolve *sds, CgState *st, const AxItem *items,
                            int nitems, int grid, int src, const BaxDir &bd,
                            hipStream_t s) {
   const size_t lds = (size_t)max_lds_words<BS, TC, N1s...>() * sizeof(TC);
-  hipLaunchKernelGGL((k_bax<BS, TV, TG, TC, DIR, N1s...>), dim3(grid), dim3(BS), lds,
+  hipLaunchKernelGGL((k_bax<BS, TV, TG, TC, DIR, STREAM, N1s...>), dim3(grid), dim3(BS), lds,
                      s, sds, st, items, nitems, src, bd);
 }
 
-template <int BS, class TV, class TG, class TC, int DIR>
+template <int BS, class TV, class TG, class TC, int DIR, bool STREAM>
 static void launch_bax_bs(int nset, const BatchSolve *sds, CgState *st,
                           const AxItem *items, int nitems, int grid, int src,
                           const BaxDir &bd, hipStream_t s) {
@@ -184,7 +211,8 @@ static void launch_bax_bs(int nset, const BatchSolve *sds, CgState *st,
   // order sets compiled: one order (n1 = 2..9) or the mixed set {4, 6, 8}
   switch (nset) {
 #define SEM_BAX(...)                                                                      \
-  launch_bax_set<BS, TV, TG, TC, DIR, __VA_ARGS__>(sds, st, items, nitems, grid, src, bd, s); \
+  launch_bax_set<BS, TV, TG, TC, DIR, STREAM, __VA_ARGS__>(sds, st, items, nitems, grid, src, \
+                                                           bd, s);                        \
   break
     case 2: SEM_BAX(2);
     case 3: SEM_BAX(3);
@@ -200,30 +228,30 @@ static void launch_bax_bs(int nset, const BatchSolve *sds, CgState *st,
   }
 }
 
-template <class TV, class TG, class TC, int DIR>
+template <class TV, class TG, class TC, int DIR, bool STREAM>
 static void launch_bax_t(int bs, int nset, const BatchSolve *sds, CgState *st,
                          const AxItem *items, int nitems, int grid, int src,
                          const BaxDir &bd, hipStream_t s) {
   switch (bs) {
-    case 64: launch_bax_bs<64, TV, TG, TC, DIR>(nset, sds, st, items, nitems, grid, src, bd, s); break;
-    case 128: launch_bax_bs<128, TV, TG, TC, DIR>(nset, sds, st, items, nitems, grid, src, bd, s); break;
-    case 256: launch_bax_bs<256, TV, TG, TC, DIR>(nset, sds, st, items, nitems, grid, src, bd, s); break;
+    case 64: launch_bax_bs<64, TV, TG, TC, DIR, STREAM>(nset, sds, st, items, nitems, grid, src, bd, s); break;
+    case 128: launch_bax_bs<128, TV, TG, TC, DIR, STREAM>(nset, sds, st, items, nitems, grid, src, bd, s); break;
+    case 256: launch_bax_bs<256, TV, TG, TC, DIR, STREAM>(nset, sds, st, items, nitems, grid, src, bd, s); break;
     default: fail(SEM_ERR_ARG, "batched operator: block size must be 64, 128 or 256");
   }
 }
 
-template <int DIR>
+template <int DIR, bool STREAM>
 static void launch_bax_d(int prec, int bs, int nset, const BatchSolve *sds, CgState *st,
                          const AxItem *items, int nitems, int grid, int src,
                          const BaxDir &bd, hipStream_t s) {
   if (prec == SEM_FP64)
-    launch_bax_t<double, double, double, DIR>(bs, nset, sds, st, items, nitems, grid, src,
+    launch_bax_t<double, double, double, DIR, STREAM>(bs, nset, sds, st, items, nitems, grid, src,
                                               bd, s);
   else if (prec == SEM_FP32)
-    launch_bax_t<float, float, float, DIR>(bs, nset, sds, st, items, nitems, grid, src, bd,
+    launch_bax_t<float, float, float, DIR, STREAM>(bs, nset, sds, st, items, nitems, grid, src, bd,
                                            s);
   else
-    launch_bax_t<float, uint16_t, float, DIR>(bs, nset, sds, st, items, nitems, grid, src,
+    launch_bax_t<float, uint16_t, float, DIR, STREAM>(bs, nset, sds, st, items, nitems, grid, src,
                                               bd, s);
 }
 
@@ -232,13 +260,15 @@ void launch_bax(int prec, int bs, int nset, const BatchSolve *sds, CgState *st,
                 hipStream_t s) {
   if (nitems <= 0) return;
   if (bd.mode == 0)
-    launch_bax_d<0>(prec, bs, nset, sds, st, items, nitems, grid, src, bd, s);
+    bd.stream ? launch_bax_d<0, true>(prec, bs, nset, sds, st, items, nitems, grid, src, bd, s)
+              : launch_bax_d<0, false>(prec, bs, nset, sds, st, items, nitems, grid, src, bd, s);
   else if (bd.mode == 1)
-    launch_bax_d<1>(prec, bs, nset, sds, st, items, nitems, grid, src, bd, s);
+    bd.stream ? launch_bax_d<1, true>(prec, bs, nset, sds, st, items, nitems, grid, src, bd, s)
+              : launch_bax_d<1, false>(prec, bs, nset, sds, st, items, nitems, grid, src, bd, s);
   else if (bd.mode == 2)
-    launch_bax_d<2>(prec, bs, nset, sds, st, items, nitems, grid, src, bd, s);
+    launch_bax_d<2, false>(prec, bs, nset, sds, st, items, nitems, grid, src, bd, s);
   else
-    launch_bax_d<3>(prec, bs, nset, sds, st, items, nitems, grid, src, bd, s);
+    launch_bax_d<3, true>(prec, bs, nset, sds, st, items, nitems, grid, src, bd, s);
   SEM_HIP(hipGetLastError());
 }
 

@@ -33,6 +33,8 @@ namespace sem {
 
 typedef short m16x4 __attribute__((ext_vector_type(4)));
 typedef float mf32x4 __attribute__((ext_vector_type(4)));
+// (the output need only be aligned to its element)
+typedef float mf32x4_u __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int MW = 4;  // waves (elements) per workgroup
 
@@ -185,9 +187,10 @@ __device__ inline void mfma_element(int l, Lds &L, const uint16_t (&gq)[6][8],
 }
 
 // the six BF16 factors of column (i, j) of element e: the column-contiguous
-// layout [E][6][64][8] at n1 = 8, [E][6][n1^3] otherwise
+// layout [E][6][64][8] at n1 = 8, [E][6][n1^3] otherwise.  nt (n1 = 8): with
+// the streaming hint, for operators beyond the last-level cache (OpShape)
 template <int N1>
-__device__ inline void load_factors(int l, bool act, int64_t e,
+__device__ inline void load_factors(int l, bool act, int64_t e, bool nt,
                                     const uint16_t *__restrict__ G_,
                                     uint16_t (&gq)[6][8]) {
   constexpr int NP = N1 * N1, N3 = NP * N1;
@@ -197,8 +200,8 @@ __device__ inline void load_factors(int l, bool act, int64_t e,
 #pragma unroll
     for (int q = 0; q < 6; ++q) {
       u32x4 v = {0u, 0u, 0u, 0u};
-      if (act)
-        v = __builtin_nontemporal_load((gp<const u32x4>)(G + e * 6 * N3 + q * N3 + 8 * l));
+      const gp<const u32x4> row = (gp<const u32x4>)(G + e * 6 * N3 + q * N3 + 8 * l);
+      if (act) v = nt ? __builtin_nontemporal_load(row) : *row;
       const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
       for (int h = 0; h < 4; ++h) {
@@ -443,7 +446,7 @@ __global__ void __launch_bounds__(64 * MW)
     k_ax_mfma(int64_t E, const uint16_t *__restrict__ Dhi,
               const uint16_t *__restrict__ Dlo, const uint16_t *__restrict__ G,
               const uint16_t *__restrict__ H, const uint16_t *__restrict__ u,
-              float *__restrict__ w) {
+              float *__restrict__ w, int nt) {
   constexpr int NP = N1 * N1, N3 = NP * N1;
   __shared__ MfmaLds lds[MW];
   const int wv = threadIdx.x >> 6, l = threadIdx.x & 63;
@@ -453,7 +456,7 @@ __global__ void __launch_bounds__(64 * MW)
   m16x4 fh, fl, bh, bl;
   d_operands<N1>(l, Dhi, Dlo, fh, fl, bh, bl);
   uint16_t gq[6][8];
-  load_factors<N1>(l, act, e, G, gq);
+  load_factors<N1>(l, act, e, nt != 0, G, gq);
   if constexpr (N1 == 8) {
     u32x4 v = {0u, 0u, 0u, 0u};
     if (act) v = *reinterpret_cast<const u32x4 *>(u + e * N3 + 8 * l);
@@ -483,9 +486,17 @@ __global__ void __launch_bounds__(64 * MW)
             bf16_to_f32((uint16_t)(wv[h] >> 16)) * bf16_to_f32(L.u[8 * l + 2 * h + 1]);
       }
     }
+    // 32 consecutive bytes per lane in two stores
+    mf32x4_u *dst = reinterpret_cast<mf32x4_u *>(w + e * N3 + 8 * l);
 #pragma unroll
-    for (int h = 0; h < 8; ++h)
-      __builtin_nontemporal_store(src[h] + hv[h], w + e * N3 + 8 * l + h);
+    for (int h = 0; h < 2; ++h) {
+      const mf32x4_u v = {src[4 * h] + hv[4 * h], src[4 * h + 1] + hv[4 * h + 1],
+                        src[4 * h + 2] + hv[4 * h + 2], src[4 * h + 3] + hv[4 * h + 3]};
+      if (nt)
+        __builtin_nontemporal_store(v, dst + h);
+      else
+        dst[h] = v;
+    }
   } else {
     for (int p = l; p < N3; p += 64) {
       const int i = p % N1, j = (p / N1) % N1, k = p / NP;
@@ -505,11 +516,12 @@ static void launch_ax_mfma_s(int N, int64_t E, const uint16_t *Dhi,
   const int64_t blocks = (E + MW - 1) / MW;
   if (blocks == 0) return;
   const dim3 grid((unsigned)blocks), block(64 * MW);
+  const int nt = ax_regime(E * (N + 1) * (N + 1) * (N + 1), 18) == AX_STREAM;
   switch (N) {
 #define SEM_AXM(NN)                                                          \
   case NN:                                                                   \
     hipLaunchKernelGGL((k_ax_mfma<NN + 1, SPLIT>), grid, block, 0, s, E, Dhi, \
-                       Dlo, G, H, u, w);                                     \
+                       Dlo, G, H, u, w, nt);                                 \
     break;
     SEM_AXM(1)
     SEM_AXM(2)
@@ -615,14 +627,14 @@ __device__ inline void gather_dir(const Box &box, const DirMfma &d, bool act, in
 // by a fixed butterfly.  Every wave of the workgroup calls it (act = false:
 // no loads or stores).
 template <int N1, bool SPLIT>
-__device__ inline void solve_elem_mfma(int l, MfmaLdsSplit &L, int64_t e, bool act,
+__device__ inline void solve_elem_mfma(int l, MfmaLdsSplit &L, int64_t e, bool act, bool nt,
                                        const Box &box, const DirMfma &dir, gp<float> w,
                                        const uint16_t *G, gp<const uint16_t> H,
                                        m16x4 fh, m16x4 fl, m16x4 bh, m16x4 bl,
                                        gp<double> edot) {
   constexpr int NP = N1 * N1, N3 = NP * N1;
   uint16_t gq[6][8];
-  load_factors<N1>(l, act, e, G, gq);
+  load_factors<N1>(l, act, e, nt, G, gq);
   float pv[8];  // the lane's column (i, j) = (l % 8, l / 8) of p', k = t
   gather_dir(
       box, dir, act, e,
@@ -696,7 +708,7 @@ __global__ void __launch_bounds__(64 * MW)
       const int64_t e = it.elem0 + e0 + wv;
       // global pointers (their address space is not known from the descriptor)
       solve_elem_mfma<N1, SPLIT>(
-          l, L, e, e0 + wv < epb && e < sd.E, sd.box, dir, (gp<float>)sd.v32[VWL],
+          l, L, e, e0 + wv < epb && e < sd.E, bd.stream, sd.box, dir, (gp<float>)sd.v32[VWL],
           (const uint16_t *)sd.G16, (gp<const uint16_t>)sd.H16, fh, fl, bh, bl,
           (gp<double>)sd.edot);
       wave_lds_sync();  // L is reused by the next element
@@ -712,7 +724,7 @@ __global__ void __launch_bounds__(64 * MW)
     k_ax_mfma_solve(int64_t E, const uint16_t *__restrict__ Dhi,
                     const uint16_t *__restrict__ Dlo, const uint16_t *__restrict__ G,
                     const uint16_t *__restrict__ H, const float *__restrict__ z,
-                    float *__restrict__ w, Box box, DirArgs<float> da, int mode,
+                    float *__restrict__ w, Box box, DirArgs<float> da, int mode, int nt,
                     double *__restrict__ edot) {
   __shared__ MfmaLdsSplit lds[MW];
   const int wv = threadIdx.x >> 6, l = threadIdx.x & 63;
@@ -726,7 +738,7 @@ __global__ void __launch_bounds__(64 * MW)
   m16x4 fh, fl, bh, bl;
   d_operands<N1>(l, Dhi, Dlo, fh, fl, bh, bl);
   const int64_t e = (int64_t)blockIdx.x * MW + wv;
-  solve_elem_mfma<N1, SPLIT>(l, lds[wv], e, e < E, box, dir, (gp<float>)w, G,
+  solve_elem_mfma<N1, SPLIT>(l, lds[wv], e, e < E, nt != 0, box, dir, (gp<float>)w, G,
                              (gp<const uint16_t>)H, fh, fl, bh, bl, (gp<double>)edot);
 }
 
@@ -812,7 +824,7 @@ __global__ void __launch_bounds__(64 * MW9)
     k_ax_mfma_solve9(int64_t E, const uint16_t *__restrict__ Dhi,
                      const uint16_t *__restrict__ Dlo, const uint16_t *__restrict__ G,
                      const uint16_t *__restrict__ H, const float *__restrict__ z,
-                     float *__restrict__ w, Box box, DirArgs<float> da, int mode,
+                     float *__restrict__ w, Box box, DirArgs<float> da, int mode, int nt,
                      double *__restrict__ edot) {
   __shared__ MfmaLds9 lds[MW9];
   const int wv = threadIdx.x >> 6, l = threadIdx.x & 63;
@@ -835,6 +847,7 @@ void launch_ax_mfma_solve(const SolveAx &a, hipStream_t s) {
   if (a.mode == 0) fail(SEM_ERR_ARG, "solve: the matrix-core operator runs inside CG only");
   const int n1 = a.N + 1;
   const bool split = a.prec == SEM_BF16_MFMA;
+  const int nt = a.regime == AX_STREAM;
   const DirArgs<float> da = {(const float *)a.p, a.mode == 3 ? nullptr : (float *)a.pnew,
                              a.st,               a.part,
                              a.nparts,           0,
@@ -843,7 +856,7 @@ void launch_ax_mfma_solve(const SolveAx &a, hipStream_t s) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)((a.E + waves - 1) / waves)), dim3(64 * waves),
                        0, s, a.E, (const uint16_t *)a.D, (const uint16_t *)a.Dlo,
                        (const uint16_t *)a.G, (const uint16_t *)a.H, (const float *)a.u,
-                       (float *)a.w, a.box, da, a.mode, a.edot);
+                       (float *)a.w, a.box, da, a.mode, nt, a.edot);
   };
   switch (n1) {
 #define SEM_AXMS(NN)                          \

@@ -18,6 +18,8 @@
 // contiguous).
 #pragma once
 
+#include <type_traits>
+
 #include "cg_dir.h"
 #include "common.h"
 #include "sem_internal.h"
@@ -50,28 +52,97 @@ template <int N1, class TC = double> constexpr int lds_words(int epb) {
   return 3 * epb * N1 * N1 * ax_pad<N1, TC>();
 }
 
-// Workgroup shape of the operator kernels per order and value size (timed on
-// the 16.8M-node meshes at every order, and again over 2-4 shapes per order
-// with and without the load predicate and the non-temporal hint; every
-// choice below is the fastest or within 1.5 % of it).  FP64: elements per workgroup chosen
-// so that EPB n1^2 fills whole waves (n1 = 8: four elements, 256 threads),
-// and the factors are read with non-temporal loads except at n1 = 2, 3, 5,
-// where one factor column is a short piece of a cache line and the
-// non-temporal hint makes the neighbouring pieces miss again.  FP32 / BF16:
-// 64-thread workgroups.  PRED: the loads carry the thread's element
-// predicate instead of reading a valid stand-in element (FP64 at n1 = 7 and
-// 9, where the unpredicated loads were 5-7 % slower; elsewhere they are
-// faster, by 12 % at n1 = 2 and 16 % at n1 = 3).
-template <int N1, int BYTES> struct OpShape {
+// Workgroup shape and load hints of the operator kernels per order, storage
+// type of the factors and size of the mesh, each timed over orders, shapes and
+// sizes of 0.06M to 16M local nodes (standalone operator: SOLVE = false; the
+// solvers' gathered one: true).  What decides:
+//  * AX_SMALL, at most 0.2M local nodes: the fewest elements that fill a wave,
+//    so that the mesh spreads over the compute units (FP64 N = 7, 0.1M nodes
+//    6.6 -> 5.2 us against four elements per workgroup).
+//  * AX_CACHED, the arrays that come round again fit the last-level cache:
+//    the operator's own up to 320 MiB (the 256 MB cache keeps most of them
+//    from one application to the next), a solve's operator and vectors up to
+//    256 MiB (24^3, N = 7, FP32 flexible CG at 314 MB: 137 ms a solve with the
+//    streaming forms, 152 ms with these): no streaming hints, which would make the next application miss
+//    (FP64 N = 7, 4M nodes 43.4 -> 37.9 us; FP32 N = 7, 8M nodes 39.5 -> 34.4;
+//    BF16 N = 1, 2M nodes 20.1 -> 6.4), and in the solvers element blocks
+//    numbered so that every XCD takes one contiguous run of them (XCD):
+//    neighbours share the gathered vector's lines in one L2 (FP64 N = 6, 2.4M
+//    nodes 51.2 -> 41.6 us, FP32 N = 7, 2.5M 29.5 -> 20.5).
+//  * AX_STREAM: the factors are read with the streaming hint only where a
+//    factor column of a wave's load covers whole cache lines (n1 = 8; n1 = 4
+//    in FP64; in the standalone operator also the other orders of NTG below).
+//    Elsewhere the hint makes the neighbouring pieces of a line miss again:
+//    16M nodes, BF16 N = 1, 2, 3, 4, 5, 6, 8: 154, 131, 71, 86, 75, 63, 84 ->
+//    37, 78, 36, 56, 46, 48, 57 us; FP32 N = 1, 2, 4: 214, 150, 104 -> 81,
+//    105, 95; solver, 12M nodes, FP64 N = 4 150 -> 134, N = 5 137 -> 130, FP32
+//    N = 3 72 -> 57, N = 8 105 -> 76.  Contiguous runs per XCD are slower here
+//    except for FP32 and BF16 at n1 = 8 (FP64 N = 5 130 -> 143, FP32 N = 5 72
+//    -> 77; FP32 N = 7 74 -> 62).
+// FP64 takes EPB elements per workgroup so that EPB n1^2 fills whole waves
+// except where one wave per element was faster.  PRED: the loads carry the
+// thread's element predicate instead of reading a valid stand-in element
+// (FP64 at n1 = 7 and 9, where the unpredicated loads were 5-7 % slower;
+// elsewhere they are faster, by 12 % at n1 = 2 and 16 % at n1 = 3).
+constexpr int64_t AX_SMALL_NODES = 200000;
+constexpr double AX_CACHE_BYTES = 320.0 * 1024 * 1024;
+constexpr double SOLVE_CACHE_BYTES = 256.0 * 1024 * 1024;
+
+// standalone operator; node_bytes: what one application moves per local node
+inline AxRegime ax_regime(int64_t nodes, int node_bytes) {
+  if (nodes <= AX_SMALL_NODES) return AX_SMALL;
+  return (double)nodes * node_bytes <= AX_CACHE_BYTES ? AX_CACHED : AX_STREAM;
+}
+// solves of nL local and nG unique nodes in all: factors of gb and vectors of
+// vb bytes a value, six vectors and the E-vector
+inline double solve_bytes(int64_t nL, int64_t nG, int gb, int vb) {
+  return (double)nL * (6 * gb + vb) + 6.0 * vb * (double)nG;
+}
+inline AxRegime solve_regime(int64_t nL, int64_t nG, int gb, int vb) {
+  if (nL <= AX_SMALL_NODES) return AX_SMALL;
+  return solve_bytes(nL, nG, gb, vb) <= SOLVE_CACHE_BYTES ? AX_CACHED : AX_STREAM;
+}
+
+template <int N1, int GB, bool SOLVE, int REG> struct OpShape {
   static constexpr int NP = N1 * N1;
-  static constexpr int EPB64 = N1 == 2 ? 64 : N1 == 3 ? 7 : N1 == 4 ? 4
-                               : N1 == 5 ? 5 : N1 == 6 ? 7 : N1 == 7 ? 5
-                               : N1 == 8 ? 4 : 3;
-  static constexpr int EPB = BYTES == 8 ? EPB64 : ((64 / NP) > 0 ? 64 / NP : 1);
+  static constexpr int FILL = (64 / NP) > 0 ? 64 / NP : 1;
+  static constexpr int pick(int a2, int a3, int a4, int a5, int a6, int a7, int a8, int a9) {
+    return N1 == 2 ? a2 : N1 == 3 ? a3 : N1 == 4 ? a4 : N1 == 5 ? a5 : N1 == 6 ? a6
+           : N1 == 7 ? a7 : N1 == 8 ? a8 : a9;
+  }
+  static constexpr int epb() {
+    if (REG == AX_SMALL) return FILL;
+    if (GB == 8 && !SOLVE) return pick(64, 7, 4, 5, 7, 5, 4, 3);
+    if (GB == 8) return REG == AX_CACHED ? pick(64, 7, 4, 5, 7, 1, 1, 3)
+                                         : pick(64, 7, 4, 5, 7, 1, 4, 3);
+    if (SOLVE) return REG == AX_STREAM && GB == 4 ? pick(16, 14, 16, 5, 7, 1, 1, 3)
+                                                  : pick(16, 14, 16, 5, 7, 5, 1, 3);
+    if (GB == 4) return REG == AX_CACHED ? pick(16, 14, 4, 2, 3, 1, 1, 1)
+                                         : pick(64, 28, 4, 2, 1, 1, 1, 1);
+    return REG == AX_CACHED ? pick(16, 14, 4, 2, 3, 1, 1, 3) : pick(16, 14, 4, 5, 3, 5, 1, 3);
+  }
+  static constexpr bool ntg() {
+    if (REG != AX_STREAM) return false;
+    if (N1 == 8) return true;
+    if (GB == 8 && SOLVE) return N1 == 4 || N1 == 7 || N1 == 9;
+    if (GB == 8) return N1 == 4 || N1 == 6 || N1 == 7 || N1 == 9;
+    return GB == 4 && !SOLVE && (N1 == 4 || N1 == 6 || N1 == 7);
+  }
+  static constexpr int EPB = epb();
   static constexpr int THREADS = EPB * NP;
-  static constexpr bool NTG = BYTES != 8 || !(N1 == 2 || N1 == 3 || N1 == 5);
-  static constexpr bool PRED = BYTES == 8 && (N1 == 7 || N1 == 9);
+  static constexpr bool NTG = ntg();
+  static constexpr bool PRED = GB == 8 && (N1 == 9 || (N1 == 7 && EPB > 1));
+  static constexpr bool XCD = SOLVE && (REG != AX_STREAM || (N1 == 8 && GB != 8));
 };
+
+// element block of workgroup b of nb: workgroups are dealt to the 8 XCDs in
+// turn (workgroup b runs on XCD b % 8), each with its own L2; XCD x = b % 8
+// takes the run [x q + min(x, r), ...) of q or q + 1 blocks (q = nb / 8, r =
+// nb % 8)
+__device__ inline int64_t xcd_run_block(unsigned b, unsigned nb) {
+  const unsigned q = nb / 8, r = nb % 8, x = b % 8, k = b / 8;
+  return (int64_t)x * q + (x < r ? x : r) + k;
+}
 
 // Apply the operator to elements e0 .. e0 + EPB - 1 (those < E) with the
 // threads t = 0 .. of one workgroup; threads t >= EPB n1^2 only join the
@@ -90,7 +161,7 @@ template <int N1, int BYTES> struct OpShape {
 // All 64 lanes of every wave must then be launched.
 template <int N1, int EPB, class TU, class TG, class TW, class TC, bool GATHER,
           bool NTW, bool MASS = false, bool NTG = true, bool EDOT = false,
-          bool PRED = false, int DIR = 0>
+          bool PRED = false, int DIR = 0, bool DESC = false>
 __device__ __forceinline__ void ax_tile(int t, int64_t e0, int64_t E,
                                         const TC *__restrict__ D_,
                                         const TG *__restrict__ G_,
@@ -105,7 +176,11 @@ __device__ __forceinline__ void ax_tile(int t, int64_t e0, int64_t E,
                 "the direction is formed at the solvers' gather");
   // every array is global memory (the batched kernel reads these pointers
   // from a descriptor, where their address space is not known)
-  const gp<const TC> D = (gp<const TC>)D_;
+  // (DESC: D comes from a descriptor; 80 vector loads an element fewer, 64 ->
+  // 47 us for 9 FP32 solves of 12^3, N = 7.  Single FP64 solves were 1 %
+  // slower with it)
+  typedef typename std::conditional<DESC, cp<TC>, gp<const TC>>::type DPtr;
+  const DPtr D = (DPtr)D_;
   const gp<const TG> G = (gp<const TG>)G_;
   const gp<const TU> u = (gp<const TU>)u_;
   const gp<TW> w = (gp<TW>)w_;
@@ -204,8 +279,8 @@ __device__ __forceinline__ void ax_tile(int t, int64_t e0, int64_t E,
   if constexpr (VEC16) {
 #pragma unroll
     for (int q = 0; q < 6; ++q) {
-      const u32x4 v =
-          __builtin_nontemporal_load((gp<const u32x4>)(G + ed * 6 * N3 + q * N3 + 8 * c));
+      const gp<const u32x4> row = (gp<const u32x4>)(G + ed * 6 * N3 + q * N3 + 8 * c);
+      const u32x4 v = NTG ? __builtin_nontemporal_load(row) : *row;
       const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
       for (int h = 0; h < 4; ++h) {

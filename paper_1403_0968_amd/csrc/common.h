@@ -52,6 +52,12 @@ template <> struct Cvt<double, float> {
 // memory (all device buffers here) access them through gp pointers.
 template <class T> using gp = T __attribute__((address_space(1))) *;
 
+// Memory that no kernel writes while this one runs.  Uniform loads through it
+// go through the scalar cache also where the pointer itself was loaded from a
+// descriptor: through gp the compiler cannot know that the kernel's own stores
+// leave them alone and makes them vector loads.
+template <class T> using cp = const T __attribute__((address_space(4))) *;
+
 // orders a wave's LDS writes before its later LDS reads of other lanes'
 // entries: the lanes of a wave execute together and a wave's LDS
 // operations complete in issue order, so only the compiler has to be kept

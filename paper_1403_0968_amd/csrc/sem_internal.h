@@ -186,12 +186,15 @@ void launch_precond(sem_handle *h, int pc, int prec, const void *r, void *z,
 // mode 1 or 2 (cg_dir.h): src is VZ and the operator acts on the new
 // direction, its beta from the solve's state (1) or from the partial sums
 // of the last r update (2).
+// size of a mesh or solve against the caches (OpShape in ax_tile.h)
+enum AxRegime { AX_SMALL = 0, AX_CACHED = 1, AX_STREAM = 2 };
 struct BaxDir {  // the direction arguments of a batch
   int32_t mode = 0;
   int32_t par = 0;               // 0: VP holds the old direction, VW the new; 1: swapped
   const double *part = nullptr;  // [2][stride] partial sums
   int32_t stride = 0;
   const int32_t *vbeg = nullptr; // per-solve ranges of the partial sums
+  bool stream = false;           // the solves exceed the last-level cache (AX_STREAM)
 };
 // persistent batched operator over (solve, element tile) items
 void launch_bax(int prec, int bs, int nset, const BatchSolve *sds, CgState *st,
@@ -209,7 +212,7 @@ struct SolveAx {
   void *w;
   Box box;
   int mode;
-  bool nt;  // store the output with the streaming hint (vectors beyond the caches)
+  AxRegime regime;
   // modes 1 to 3
   const void *p;
   void *pnew;

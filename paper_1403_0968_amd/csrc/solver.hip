@@ -43,6 +43,7 @@
 #include <string>
 
 #include "assemble.h"
+#include "ax_tile.h"
 #include "cg_dir.h"
 #include "common.h"
 #include "sem_internal.h"
@@ -834,7 +835,11 @@ struct sem_batch {
   std::vector<sem::VecItem> h_vis;
   std::vector<sem::AxItem> h_ax[3];
   std::vector<int32_t> h_vbeg, h_axbeg[3];  // per-solve item ranges
-  int bs[5] = {128, 64, 64, 256, 256};  // operator block size per precision
+  // operator block size per precision: 256 threads hold about the elements per
+  // workgroup that the single-solve operator takes (OpShape); FP32 operator of
+  // 24 solves of 11.6M nodes, N in {3, 5, 7}: 64, 128 and 256 threads 94, 90
+  // and 84 us
+  int bs[5] = {256, 256, 256, 256, 256};
   int gmul[5] = {0, 0, 0, 0, 0};  // persistent grid = 256 CUs x gmul (0: 1 item/WG)
   sem::CgState *host_st = nullptr;
   double *host_red = nullptr;
@@ -1036,14 +1041,24 @@ void destroy_ws(sem_handle *h) {
 // assembly + r update at 11.4M unique nodes: 114 -> 104 us)
 static int vec_grid(const sem_batch *b) { return b->n_vi; }
 
-// Streaming (non-temporal) hints on the solver's vectors and operator output
-// when the batch's vectors (about five unique-node vectors and the E-vector,
-// of `tv` bytes per value) exceed half of the 256 MB last-level cache: their
-// next use is then an iteration away and they would not stay cached anyway;
-// smaller solves keep the normal hints and their vectors stay cached.
+// Streaming (non-temporal) hints on the solver's vectors and operator output,
+// and a pass of its own for p and x (cg_dir.h), when the batch's vectors
+// (about five unique-node vectors and the E-vector, of `tv` bytes per value)
+// exceed half of the 256 MB last-level cache: their next use is then an
+// iteration away and they would not stay cached anyway; smaller solves keep
+// the normal hints and their vectors stay cached.  The same with vectors and
+// factors (of `gb` bytes) together beyond 300 MiB: us per iteration fused and
+// with the pass, FP32 N = 5 7.8M nodes (328 MB) 112 and 101, FP64 N = 5 3.8M
+// (321 MB) 97 and 91; FP64 N = 3 4.1M (311 MB) 94 and 105, FP32 N = 3 8M
+// (306 MB) 109 and 113, BF16 N = 5 7.8M (234 MB) 83 and 90.
 constexpr double NT_BYTES = 128.0 * 1024 * 1024;
-static int stream_vectors(const sem_batch *b, size_t tv) {
-  return (double)tv * (5.0 * (double)b->sum_nG + (double)b->sum_nL) > NT_BYTES ? 1 : 0;
+constexpr double FUSE_BYTES = 300.0 * 1024 * 1024;
+static int stream_vectors(const sem_batch *b, size_t tv, size_t gb) {
+  return (double)tv * (5.0 * (double)b->sum_nG + (double)b->sum_nL) > NT_BYTES ||
+         solve_bytes(b->sum_nL, b->sum_nG, (int)gb, (int)tv) > FUSE_BYTES;
+}
+static size_t factor_bytes(int prec) {
+  return prec == SEM_FP64 ? 8 : prec == SEM_FP32 ? 4 : 2;
 }
 
 // the work lists of the CG iteration kernels: compacted while run_cg has
@@ -1126,6 +1141,8 @@ static void bax(sem_batch *b, int prec, int src, int mode) {
                       "order N <= 8");
   CgState *st = b->st.as<CgState>();
   const double *part = b->part.as<double>();
+  const AxRegime regime =
+      solve_regime(b->sum_nL, b->sum_nG, (int)factor_bytes(prec), prec == SEM_FP64 ? 8 : 4);
   if (b->n == 1) {  // a single solve: every argument passed in
     const BatchSolve &d = b->hsd[0];
     sem_handle *h = b->hs[0];
@@ -1143,7 +1160,7 @@ static void bax(sem_batch *b, int prec, int src, int mode) {
     a.w = v(VWL);
     a.box = d.box;
     a.mode = mode;
-    a.nt = stream_vectors(b, f64 ? 8 : 4) != 0;
+    a.regime = regime;
     a.p = v(b->par ? VW : VP);
     a.pnew = v(b->par ? VP : VW);
     a.st = st;
@@ -1162,6 +1179,7 @@ static void bax(sem_batch *b, int prec, int src, int mode) {
   bd.part = part;
   bd.stride = it_nvi(b);
   bd.vbeg = it_vbeg(b);
+  bd.stream = regime == AX_STREAM;
   // the matrix-core operator takes the tiles of the 256-thread item list
   const int bs = mfma ? 256 : b->bs[prec];
   const int k = bs_slot(bs);
@@ -1222,7 +1240,7 @@ static void iteration_t(sem_batch *b, int prec, int jac, bool last) {
   double *part = b->part.as<double>();
   const VecItem *vi = it_vitems(b);
   const int nv = it_nvi(b), n = b->n;
-  const bool fused = stream_vectors(b, sizeof(TV)) == 0;
+  const bool fused = stream_vectors(b, sizeof(TV), factor_bytes(prec)) == 0;
   const bool redp = fused && reduce_parts(b), rede = fused && reduce_energies(b);
   const int form = !fused ? 0 : rede ? 2 : 1;
   bax(b, prec, fused ? VZ : VP, !fused ? 3 : redp ? 2 : 1);
@@ -1258,7 +1276,7 @@ static void iteration_fcg_t(sem_batch *b, int prec) {
   const int nv = b->n_vi, n = b->n;
   sem_handle *h = b->hs[0];
   const bool f32 = sizeof(TV) == 4;
-  const bool fused = stream_vectors(b, sizeof(TV)) == 0;
+  const bool fused = stream_vectors(b, sizeof(TV), factor_bytes(prec)) == 0;
   const bool rede = fused && reduce_energies(b);
   bax(b, prec, fused ? VZ : VP, fused ? 1 : 3);
   if (!rede)

@@ -118,3 +118,39 @@ def test_limits_match_oracle_iterates(sem, N, box):
     err = np.linalg.norm(to_host(x) - xo) / np.linalg.norm(xo)
     assert err <= 1e-8, err
     pr.close()
+
+
+# a mesh of its own size class alone (the single-solve operator in the shapes
+# for meshes in and beyond the caches) against the batched operator beside a
+# small partner: the same bits
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("N", range(1, 9))
+def test_single_shapes_equal_batched(sem, N, prec):
+    print(f"[gpu] single against batch N={N} {prec}", flush=True)
+    t = torch()
+    p = {"fp64": sem.SEM_FP64, "fp32": sem.SEM_FP32, "bf16": sem.SEM_BF16}[prec]
+    value = 8 if prec == "fp64" else 4
+    per_node = value * (1 + 5 * (N / (N + 1)) ** 3)  # vectors, bytes per local node
+    small = sem.sem_setup(N, 2, 2, 3)
+    try:
+        # 0.9M nodes (in the caches; ragged so that the last workgroup is
+        # partial), and vectors beyond 128 MiB
+        n = _side(N, 0.9e6)
+        big = _side(N, 1.2 * 128 * 2 ** 20 / per_node)
+        for box in ((n, n + 1, n), (big, big, big + 1)):
+            h = sem.sem_setup(N, *box, mapping=sem.SEM_MAP_SINE_CYCLIC)
+            b, b0 = _rhs(sem, h, 3), _rhs(sem, small, 4)
+            kw = dict(rtol=1e-9, maxit=5, inner_prec=p, inner_rtol=1e-2, check_every=4,
+                      raise_on_fail=False)
+            x = t.zeros_like(b)
+            sem.sem_pcg_solve(h, b, x, **kw)
+            bt = sem.sem_batch_create([small, h])
+            xs = [t.zeros_like(b0), t.zeros_like(b)]
+            sem.sem_batch_pcg_solve(bt, [b0, b], xs, **kw)
+            t.cuda.synchronize()
+            sem.sem_batch_destroy(bt)
+            off = float((x - xs[1]).abs().max() / x.abs().max())
+            sem.sem_destroy(h)
+            assert off == 0.0, (box, off)
+    finally:
+        sem.sem_destroy(small)
