@@ -166,8 +166,31 @@ void launch_precond(sem_handle *h, int pc, int prec, const void *r, void *z,
 // ---------------------------------------------------------------------------
 struct SrcParams {
   int kind, nmodes;
-  double k[64][3], a[64], phi[64];
+  double k[64][3], a[64], phi[64];  // phi in turns
 };
+
+// cos(2 pi t). t - rint(t) is exact, so no reduction by a rounded pi is left;
+// folded to sin(2 pi c), |c| <= 1/4, and summed as its Taylor series through
+// the 21st power (the first term left out is 1.3e-18 at pi / 2).  Bound by
+// the FP64 rate: about 20 instructions a mode; with the library's cos, which
+// takes any angle, the load vector of 8 modes took 148 us at 24^3, N = 7,
+// with this 85 (error against 64 bits no larger, at phases of 1e5 2000 times
+// smaller).
+__device__ __forceinline__ double cos_turns(double t) {
+  const double c = 0.25 - fabs(t - rint(t));
+  const double y = 6.28318530717958647693 * c, q = y * y;
+  double s = 1.0 / 51090942171709440000.0;
+  s = fma(-q, s, 1.0 / 121645100408832000.0);
+  s = fma(-q, s, 1.0 / 355687428096000.0);
+  s = fma(-q, s, 1.0 / 1307674368000.0);
+  s = fma(-q, s, 1.0 / 6227020800.0);
+  s = fma(-q, s, 1.0 / 39916800.0);
+  s = fma(-q, s, 1.0 / 362880.0);
+  s = fma(-q, s, 1.0 / 5040.0);
+  s = fma(-q, s, 1.0 / 120.0);
+  s = fma(-q, s, 1.0 / 6.0);
+  return fma(-q * y, s, y);
+}
 
 __global__ void k_rhs_local(int64_t nL, const double *__restrict__ X,
                             const double *__restrict__ B, SrcParams p,
@@ -181,8 +204,8 @@ __global__ void k_rhs_local(int64_t nL, const double *__restrict__ X,
     f = 3.0 * pi * pi * sin(pi * x) * sin(pi * y) * sin(pi * z);
   } else {
     for (int m = 0; m < p.nmodes; ++m)
-      f += p.a[m] * cos(2.0 * pi * (p.k[m][0] * x + p.k[m][1] * y +
-                                   p.k[m][2] * z) + p.phi[m]);
+      f += p.a[m] * cos_turns(p.k[m][0] * x + p.k[m][1] * y +
+                              p.k[m][2] * z + p.phi[m]);
   }
   b[l] = B[l] * f;
 }
@@ -199,7 +222,9 @@ void launch_rhs(sem_handle *h, const sem_source *src, double *b, hipStream_t s) 
     for (int m = 0; m < p.nmodes; ++m) {
       for (int d = 0; d < 3; ++d) p.k[m][d] = src->k[3 * m + d];
       p.a[m] = src->a[m];
-      p.phi[m] = src->phi[m];
+      // to turns in [-1/2, 1/2], the angle reduced by the exact pi
+      const long double w = src->phi[m];
+      p.phi[m] = (double)(atan2l(sinl(w), cosl(w)) / 6.28318530717958647692528676655900577L);
     }
   } else if (src->kind != SEM_SRC_SINE) {
     fail(SEM_ERR_ARG, "sem_rhs: unknown source kind");
