@@ -274,40 +274,29 @@ __host__ __device__ inline CopyTerms<IT> copy_terms(const Box &b, const Coord3 &
   return c;
 }
 
+template <class TV> __host__ __device__ inline TV pick(bool c, TV a, TV b) {
+  return c ? a : b;
+}
+
 // sum of the (up to 8) copies of a node, v[4 a + 2 b + c] holding copy a
 // along z, b along y, c along x (+0.0 for an absent copy, which leaves the
 // sum unchanged bit for bit: it starts at +0.0 and so is never -0.0), in
 // ascending local index: the box's direction order (copy_order)
 template <class TV> __host__ __device__ inline TV sum_copies(int order, const TV (&v)[8]) {
-  TV s = TV(0);
-#define SEM_SUM3(A, B, C)                                  \
-  _Pragma("unroll") for (int A = 0; A < 2; ++A)            \
-    _Pragma("unroll") for (int B = 0; B < 2; ++B)          \
-      _Pragma("unroll") for (int C = 0; C < 2; ++C) s = s + v[4 * a + 2 * b + c];
-  switch (order) {
-    case 0: {
-      SEM_SUM3(a, b, c)
-      break;
-    }
-    case 1: {
-      SEM_SUM3(b, c, a)
-      break;
-    }
-    case 2: {
-      SEM_SUM3(a, c, b)
-      break;
-    }
-    case 3: {
-      SEM_SUM3(c, a, b)
-      break;
-    }
-    default: {
-      SEM_SUM3(b, a, c)
-      break;
-    }
-  }
-#undef SEM_SUM3
-  return s;
+  // entries moved to the z y x positions by selects of values (in a switch
+  // over the orders, or with selects of elements, the compiler indexed the
+  // array, which put it in scratch memory)
+  const TV v1 = v[1], v2 = v[2], v3 = v[3], v4 = v[4], v5 = v[5], v6 = v[6];
+  const bool o1 = order == 1, o12 = o1 || order == 2, o14 = o1 || order == 4,
+             o3 = order == 3, o23 = o3 || order == 2, o34 = o3 || order == 4;
+  TV s = TV(0) + v[0];
+  s = s + pick(o1, v4, pick(o23, v2, v1));
+  s = s + pick(o12, v1, pick(o34, v4, v2));
+  s = s + pick(o14, v5, pick(o3, v6, v3));
+  s = s + pick(o14, v2, pick(o3, v1, v4));
+  s = s + pick(o12, v6, pick(o34, v3, v5));
+  s = s + pick(o1, v3, pick(o23, v5, v6));
+  return s + v[7];
 }
 
 }  // namespace sem
