@@ -349,6 +349,7 @@ __global__ void __launch_bounds__(64 * CA_WAVES)
     for (int i = 0; i < MR; ++i) mv[i] = t + 64 * i < KK ? Me[t + 64 * i] : 0.f;
   };
   if (e < E) fetch(e);
+  double prc = 0.0, pcw = 0.0;  // FUSE: this lane's (r_I, c), (c, w_I) terms
   for (; e < E; e += stride) {
     TV rcur[FUSE ? M : 1];  // this element's r (rv is refilled by the prefetch)
     if constexpr (FUSE) {
@@ -454,7 +455,6 @@ __global__ void __launch_bounds__(64 * CA_WAVES)
     }
     wave_lds_sync();
     // direction i: lane = pencil, M contiguous interior nodes
-    double prc = 0.0, pcw = 0.0;  // FUSE: this lane's (r_I, c), (c, w_I) terms
     if (t < P) {
       float v[Q];
 #pragma unroll
@@ -475,14 +475,6 @@ __global__ void __launch_bounds__(64 * CA_WAVES)
         }
       }
     }
-    if constexpr (FUSE) {
-      prc = wave_sum(prc);
-      pcw = wave_sum(pcw);
-      if (t == 0) {
-        epart[e] = prc;
-        epart[E + e] = pcw;
-      }
-    }
     if (!UNIQUE)  // the faces of the element carry no correction
       for (int p = t; p < N3; p += 64) {
         const int i = p % N1, j = (p / N1) % N1, k = p / (N1 * N1);
@@ -490,6 +482,26 @@ __global__ void __launch_bounds__(64 * CA_WAVES)
       }
     wave_lds_sync();  // the LDS region is rewritten for the next element
   }
+  if constexpr (FUSE) {
+    __shared__ double sm[2 * CA_WAVES];
+    prc = wave_sum(prc);
+    pcw = wave_sum(pcw);
+    if (t == 0) {
+      sm[wave] = prc;
+      sm[CA_WAVES + wave] = pcw;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+      double a = 0.0;
+#pragma unroll
+      for (int q = 0; q < CA_WAVES; ++q) a += sm[threadIdx.x * CA_WAVES + q];
+      epart[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = a;
+    }
+  }
+}
+
+int learn_epart_count(const sem_handle *h) {
+  return (int)((h->E + CA_WAVES - 1) / CA_WAVES);
 }
 
 // device damping of the attached correction (network or exact operators)
@@ -502,8 +514,7 @@ template <class TV, bool UNIQUE, int M, int Q, bool FUSE>
 static void launch_ca(const sem_handle *h, const Learn *L, const TV *r, float *out,
                       TV *zf, const TV *wL, double *epart, hipStream_t s) {
   const Box box = UNIQUE ? make_box(h->N, h->ex, h->ey, h->ez, h->dirichlet, h->periodic) : Box{};
-  const int64_t groups = (h->E + CA_WAVES - 1) / CA_WAVES;
-  const unsigned grid = (unsigned)groups;
+  const unsigned grid = (unsigned)learn_epart_count(h);
   hipLaunchKernelGGL((k_coarse_apply<TV, UNIQUE, M, Q, FUSE>), dim3(grid),
                      dim3(64 * CA_WAVES), 0, s, h->E, box, L->tab, L->Sc.as<float>(), r,
                      L->Ml.as<float>(), learn_damping_dev(h), out, zf, wL, epart);
@@ -780,7 +791,7 @@ void learn_apply(sem_handle *h, const void *r, bool f32, hipStream_t s) {
 }
 
 // flexible CG: z (holding dinv o r) += c(r) on the element interiors, and
-// the element terms of (r, c) and (c, w) into epart ([2][E], learn_epart)
+// the terms of (r, c) and (c, w) into learn_epart ([2][learn_epart_count])
 void learn_apply_fused(sem_handle *h, const void *r, void *z, const void *wL,
                        bool f32, hipStream_t s) {
   if (!learn_active(h))

@@ -285,6 +285,7 @@ void learn_apply(sem_handle *h, const void *r, bool f32, hipStream_t s);
 void learn_apply_fused(sem_handle *h, const void *r, void *z, const void *wL,
                        bool f32, hipStream_t s);
 double *learn_epart(sem_handle *h);
+int learn_epart_count(const sem_handle *h);  // terms per row, one a workgroup
 void learn_attach_exact(sem_handle *h, double damping);
 bool learn_active(const sem_handle *h);
 double learn_damping(const sem_handle *h);

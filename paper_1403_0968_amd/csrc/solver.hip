@@ -164,17 +164,18 @@ __global__ void __launch_bounds__(AT)
   if (st[s].done != 0 || (fused && st[s].done_b != 0)) return;
   gp<const double> ed = (gp<const double>)sds[s].edot;
   const int64_t E = sds[s].E;
-  constexpr int PF = 32;  // 32768 elements: every energy loaded at once
+  // 32768 elements: every energy loaded at once, also of a last round that
+  // is not full (its loads one after the other: 5.8 us at 13824 elements,
+  // so 4.7)
+  constexpr int PF = 32;
   double acc = 0.0;
-  int64_t q = threadIdx.x;
-  for (; q + (PF - 1) * AT < E; q += PF * AT) {
+  for (int64_t q = threadIdx.x; q < E; q += PF * AT) {
     double v[PF];
 #pragma unroll
-    for (int u = 0; u < PF; ++u) v[u] = ed[q + u * AT];
+    for (int u = 0; u < PF; ++u) v[u] = q + u * AT < E ? ed[q + u * AT] : 0.0;
 #pragma unroll
     for (int u = 0; u < PF; ++u) acc += v[u];
   }
-  for (; q < E; q += AT) acc += ed[q];
   const double pw = block_sum<AT>(acc, sm);
   if (threadIdx.x == 0) {
     st[s].pw = pw;
@@ -692,17 +693,17 @@ __global__ void __launch_bounds__(RT)
 
 // flexible CG (Notay's, one stored direction): beta = -(z, A p) / (p, A p),
 // convergence on (r, r), for one solve whose correction step stored its
-// element terms of (r, c) and (c, w) in epart ([2][E]): (r, z) and (z, w)
-// are the partials of the r update plus those terms
+// terms of (r, c) and (c, w) in epart ([2][ne]): (r, z) and (z, w) are the
+// partials of the r update plus those terms
 __global__ void __launch_bounds__(RT)
     k_bbeta_fcg_e(CgState *st, const double *__restrict__ part, int nitems,
-                  const double *__restrict__ epart, int E) {
+                  const double *__restrict__ epart, int ne) {
   __shared__ double sm[RT / 64];
   CgState &cs = st[0];
   if (cs.done != 0) return;
   double acc[3], ea[2];
   strided_sums<3>(part, nitems, 0, nitems, acc);
-  strided_sums<2>(epart, E, 0, E, ea);
+  strided_sums<2>(epart, ne, 0, ne, ea);
   const double rz = block_sum<RT>(acc[0] + ea[0], sm);
   const double zw = block_sum<RT>(acc[1] + ea[1], sm);
   const double rr = block_sum<RT>(acc[2], sm);
@@ -1289,7 +1290,7 @@ static void iteration_fcg_t(sem_batch *b, int prec) {
   learn_apply_fused(h, f32 ? d.v32[VR] : d.v64[VR], f32 ? d.v32[VZ] : d.v64[VZ],
                     f32 ? d.v32[VWL] : d.v64[VWL], f32, b->s);
   hipLaunchKernelGGL(k_bbeta_fcg_e, dim3(1), dim3(RT), 0, b->s, st, part, nv,
-                     learn_epart(h), (int)h->E);
+                     learn_epart(h), learn_epart_count(h));
   if (fused)
     b->par ^= 1;
   else
