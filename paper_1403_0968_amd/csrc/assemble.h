@@ -33,7 +33,7 @@ __device__ __forceinline__ TV assemble_node(const Box &bx, gp<const TV> wL, cons
                          (c ? ct.x.t1 : ct.x.t0);
           v[4 * a + 2 * b + c] = ok ? wL[lid] : TV(0);
         }
-    sw = sum_copies(PER ? bx.order : 0, v);
+    sw = sum_copies<PER>(bx.order, v);
   }
   return sw;
 }

@@ -140,7 +140,7 @@ __global__ void __launch_bounds__(RT)
               const int64_t lid = ok ? copy_lid(bx, nc, a, b, c) : 0;
               v[4 * a + 2 * b + c] = ok ? wL[lid] : TV(0);
             }
-        s = sum_copies(PER ? bx.order : 0, v);
+        s = sum_copies<PER>(bx.order, v);
       }
       wG[g] = s;
       if (DOT) acc += (double)p[g] * (double)s;
@@ -155,28 +155,73 @@ __global__ void __launch_bounds__(RT)
 // alpha_s = rz_s / (p, A p)_s with (p, A p) the sum of the solve's element
 // energies in element order (strided over the workgroup's threads, then the
 // fixed workgroup sum), one workgroup of AT threads per solve; runs between
-// the operator and the r update
+// the operator and the r update.  A solve of more than EN_DIRECT elements is
+// summed in chunks of EN_CHUNK by k_benergies first: one workgroup draws
+// what one compute unit can load and was the longest kernel of an iteration
+// on fine meshes of low order (FP64: 128^3, N = 1 331 us of 590, 80^3, N = 2
+// 81 of 362, 48^3, N = 4 21 of 304; in chunks the two kernels take 5 + 5).
+// At EN_DIRECT the one workgroup takes 6 us, less than two launches.  The
+// rule looks at the solve alone: it gives the same bits in a batch.
+constexpr int EN_PF = 32;  // energies per thread, all loaded at once
+constexpr int64_t EN_DIRECT = (int64_t)EN_PF * AT;
+constexpr int EN_CPF = 8;
+constexpr int64_t EN_CHUNK = (int64_t)EN_CPF * AT;
+
+template <int PF>
+__device__ inline double energy_sum(gp<const double> ed, int64_t n, double *sm) {
+  double acc = 0.0;
+  int64_t q0 = 0;
+  for (; q0 + PF * AT <= n; q0 += PF * AT) {  // whole rounds
+    double v[PF];
+#pragma unroll
+    for (int u = 0; u < PF; ++u) v[u] = ed[q0 + u * AT + threadIdx.x];
+#pragma unroll
+    for (int u = 0; u < PF; ++u) acc += v[u];
+  }
+  if (q0 < n) {
+    const int left = (int)(n - q0), t = threadIdx.x;
+    double v[PF];
+#pragma unroll
+    for (int u = 0; u < PF; ++u) v[u] = t + u * AT < left ? ed[q0 + u * AT + t] : 0.0;
+#pragma unroll
+    for (int u = 0; u < PF; ++u) acc += v[u];
+  }
+  return block_sum<AT>(acc, sm);
+}
+
+// sums of the chunks of solve s to esum[ebeg[s] ...]; per: chunks of the
+// largest solve.  The sums lie in the rows of (r, z) partials, which the
+// operator has read and the r update writes anew: a solve has at least one
+// unique node per element, so its ceil(nG / VCH) entries hold
+// ceil(E / EN_CHUNK) (EN_CHUNK >= VCH; periodic N = 1 has nG = E).
 __global__ void __launch_bounds__(AT)
-    k_balpha_e(const BatchSolve *__restrict__ sds, CgState *st, int fused) {
+    k_benergies(const BatchSolve *__restrict__ sds, const CgState *__restrict__ st, int fused,
+                int per, const int32_t *__restrict__ ebeg, double *__restrict__ esum) {
+  __shared__ double sm[AT / 64];
+  const int s = blockIdx.x / per, c = blockIdx.x - s * per;
+  const int64_t E = sds[s].E, e0 = c * EN_CHUNK;
+  if (E <= EN_DIRECT || e0 >= E) return;
+  if (st[s].done != 0 || (fused && st[s].done_b != 0)) return;
+  const double t = energy_sum<EN_CPF>((gp<const double>)sds[s].edot + e0,
+                                      min(E - e0, EN_CHUNK), sm);
+  if (threadIdx.x == 0) esum[ebeg[s] + c] = t;
+}
+
+__global__ void __launch_bounds__(AT)
+    k_balpha_e(const BatchSolve *__restrict__ sds, CgState *st, int fused,
+               const int32_t *__restrict__ ebeg, const double *__restrict__ esum) {
   __shared__ double sm[AT / 64];
   const int s = blockIdx.x;
   if (threadIdx.x == 0) st[s].xupd = 0;  // no x update from an earlier step
   if (st[s].done != 0 || (fused && st[s].done_b != 0)) return;
-  gp<const double> ed = (gp<const double>)sds[s].edot;
   const int64_t E = sds[s].E;
-  // 32768 elements: every energy loaded at once, also of a last round that
-  // is not full (its loads one after the other: 5.8 us at 13824 elements,
-  // so 4.7)
-  constexpr int PF = 32;
-  double acc = 0.0;
-  for (int64_t q = threadIdx.x; q < E; q += PF * AT) {
-    double v[PF];
-#pragma unroll
-    for (int u = 0; u < PF; ++u) v[u] = q + u * AT < E ? ed[q + u * AT] : 0.0;
-#pragma unroll
-    for (int u = 0; u < PF; ++u) acc += v[u];
-  }
-  const double pw = block_sum<AT>(acc, sm);
+  // every energy loaded at once, also of a last round that is not full (its
+  // loads one after the other: 5.8 us at 13824 elements, so 4.7)
+  const double pw =
+      E > EN_DIRECT
+          ? energy_sum<EN_CPF>((gp<const double>)esum + ebeg[s],
+                               (E + EN_CHUNK - 1) / EN_CHUNK, sm)
+          : energy_sum<EN_PF>((gp<const double>)sds[s].edot, E, sm);
   if (threadIdx.x == 0) {
     st[s].pw = pw;
     if (!(pw > 0.0) || !isfinite(pw))
@@ -227,8 +272,16 @@ __device__ __forceinline__ void xr_asm_chunk(const Box &bx, const XrVecs<TV, TD>
   constexpr bool FUSED = FORM != 0, RED = FORM == 2, NT = !FUSED;
   const gp<const CgState> st = (gp<const CgState>)st_;
   // the step this chunk belongs to (uniform); see CgState for who writes what
-  int done = FUSED ? st->done_b : st->done;
-  if (!FUSED && done != 0) return;
+  int done;
+  double alpha = 0.0;
+  if constexpr (FUSED) {
+    done = st->done_b;
+    if constexpr (!RED) alpha = st->alpha;
+  } else {
+    done = st->done;
+    if (done != 0) return;
+    alpha = st->alpha;
+  }
   const int64_t end = min(start + (int64_t)VCH, a.nG);
   // w_G at the node with coordinates pc (32-bit local indices unless W64:
   // some local index of the batch needs more)
@@ -272,7 +325,6 @@ __device__ __forceinline__ void xr_asm_chunk(const Box &bx, const XrVecs<TV, TD>
       }
       box_advance(bx, step, pc);
     }
-    double alpha = 0.0;
     if constexpr (FUSED) {
       double pw = 0.0;
       const double rz_b = st->rz_b;
@@ -282,8 +334,6 @@ __device__ __forceinline__ void xr_asm_chunk(const Box &bx, const XrVecs<TV, TD>
           alpha = rz_b / pw;
           if (!(pw > 0.0) || !isfinite(pw)) done = 2;
         }
-      } else {
-        alpha = st->alpha;
       }
       if (start == 0 && threadIdx.x == 0) {
         const gp<CgState> w = (gp<CgState>)st_;
@@ -295,8 +345,6 @@ __device__ __forceinline__ void xr_asm_chunk(const Box &bx, const XrVecs<TV, TD>
         if (RED && done == 0) w->pw = pw;
       }
       if (done != 0) return false;
-    } else {
-      alpha = st->alpha;
     }
     const TV al = (TV)alpha;
 #pragma unroll
@@ -469,14 +517,17 @@ __global__ void __launch_bounds__(RT)
   }
 }
 
-// the same for the chunks of a single solve
+// the same for the chunks of a single solve, last chunk first: the r update
+// has just written the end of z, which is still in the last-level cache
+// (FP64 N = 7 solves per iteration: 24^3 162.8 -> 162.3 us, 32^3 347.0 ->
+// 345.6, 40^3 664.8 -> 659.2)
 template <class TV, class TD>
 __global__ void __launch_bounds__(RT)
     k_p_1(Vecs1<TV, TD> a, const CgState *__restrict__ st) {
   const CgState &c = *st;
   if (c.xupd == 0) return;
   p_chunk<TV>((gp<const TV>)a.z, (gp<TV>)a.p, (gp<TV>)a.x, (TV)c.alpha, (TV)c.beta,
-                  c.done == 0, (int64_t)blockIdx.x * VCH, a.nG);
+                  c.done == 0, (int64_t)(gridDim.x - 1 - blockIdx.x) * VCH, a.nG);
 }
 
 // r = b - w (x0_zero: r = b and x = 0), z = dinv r, p = z; partials of
@@ -1230,6 +1281,21 @@ static Vecs1<TV, TD> vecs1(const sem_batch *b, int jac, bool fused) {
     }                                                      \
   } while (0)
 
+// alpha of every solve from the element energies
+static void launch_alpha(sem_batch *b, bool fused) {
+  const BatchSolve *sds = b->sds.as<BatchSolve>();
+  CgState *st = b->st.as<CgState>();
+  double *part = b->part.as<double>();
+  int64_t E = 0;
+  for (const BatchSolve &d : b->hsd) E = std::max(E, d.E);
+  const int per = (int)((E + EN_CHUNK - 1) / EN_CHUNK);
+  if (E > EN_DIRECT)
+    hipLaunchKernelGGL(k_benergies, dim3((unsigned)(per * b->n)), dim3(AT), 0, b->s, sds, st,
+                       fused ? 1 : 0, per, it_vbeg(b), part);
+  hipLaunchKernelGGL(k_balpha_e, dim3(b->n), dim3(AT), 0, b->s, sds, st, fused ? 1 : 0,
+                     it_vbeg(b), part);
+}
+
 // One iteration (see the head of this file); last: no iteration follows in
 // this launch sequence, so that beta and the convergence flag are brought up
 // to date for the host.  The state's sums go to the same bits whichever
@@ -1246,7 +1312,7 @@ static void iteration_t(sem_batch *b, int prec, int jac, bool last) {
   const int form = !fused ? 0 : rede ? 2 : 1;
   bax(b, prec, fused ? VZ : VP, !fused ? 3 : redp ? 2 : 1);
   if (!rede)
-    hipLaunchKernelGGL(k_balpha_e, dim3(n), dim3(AT), 0, b->s, sds, st, fused ? 1 : 0);
+    launch_alpha(b, fused);
   if (n == 1)
     SEM_XR_LAUNCH(b, form, (k_xr_asm_1<TV, TD, false, PER_, W64_, FORM_>), dim3(nv),
                   dim3(RT), 0, b->s, vecs1<TV, TD>(b, jac, fused), st, nv, part);
@@ -1274,15 +1340,14 @@ template <class TV, class TD>
 static void iteration_fcg_t(sem_batch *b, int prec) {
   CgState *st = b->st.as<CgState>();
   double *part = b->part.as<double>();
-  const int nv = b->n_vi, n = b->n;
+  const int nv = b->n_vi;
   sem_handle *h = b->hs[0];
   const bool f32 = sizeof(TV) == 4;
   const bool fused = stream_vectors(b, sizeof(TV), factor_bytes(prec)) == 0;
   const bool rede = fused && reduce_energies(b);
   bax(b, prec, fused ? VZ : VP, fused ? 1 : 3);
   if (!rede)
-    hipLaunchKernelGGL(k_balpha_e, dim3(n), dim3(AT), 0, b->s, b->sds.as<BatchSolve>(), st,
-                       fused ? 1 : 0);
+    launch_alpha(b, fused);
   SEM_XR_LAUNCH(b, !fused ? 0 : rede ? 2 : 1,
                 (k_xr_asm_1<TV, TD, true, PER_, W64_, FORM_>), dim3(nv), dim3(RT), 0,
                 b->s, vecs1<TV, TD>(b, 1, fused), st, nv, part);

@@ -282,7 +282,15 @@ template <class TV> __host__ __device__ inline TV pick(bool c, TV a, TV b) {
 // along z, b along y, c along x (+0.0 for an absent copy, which leaves the
 // sum unchanged bit for bit: it starts at +0.0 and so is never -0.0), in
 // ascending local index: the box's direction order (copy_order)
-template <class TV> __host__ __device__ inline TV sum_copies(int order, const TV (&v)[8]) {
+// ANY = false: the order is z y x (no periodic direction).
+template <bool ANY, class TV>
+__host__ __device__ inline TV sum_copies(int order, const TV (&v)[8]) {
+  if constexpr (!ANY) {
+    TV s = TV(0);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) s = s + v[q];
+    return s;
+  }
   // entries moved to the z y x positions by selects of values (in a switch
   // over the orders, or with selects of elements, the compiler indexed the
   // array, which put it in scratch memory)
