@@ -66,8 +66,8 @@ static void launch_reg(int64_t E, const void *D, const void *G, const void *H,
 template <int N1, class TU, class TG, class TW, class TC, bool MASS>
 static void launch_mass(int64_t E, const void *D, const void *G, const void *H,
                         const void *u, void *w, hipStream_t s) {
-  const AxRegime reg =
-      ax_regime(E * N1 * N1 * N1, (int)(6 * sizeof(TG) + sizeof(TU) + sizeof(TW)));
+  const AxRegime reg = ax_regime(
+      E * N1 * N1 * N1, (int)((MASS ? 7 : 6) * sizeof(TG) + sizeof(TU) + sizeof(TW)));
   if (reg == AX_SMALL)
     launch_reg<N1, TU, TG, TW, TC, MASS, AX_SMALL>(E, D, G, H, u, w, s);
   else if (reg == AX_CACHED)

@@ -60,11 +60,11 @@ template <int N1, class TC = double> constexpr int lds_words(int epb) {
 //    so that the mesh spreads over the compute units (FP64 N = 7, 0.1M nodes
 //    6.6 -> 5.2 us against four elements per workgroup).
 //  * AX_CACHED, the arrays that come round again fit the last-level cache:
-//    the operator's own up to 320 MiB (the 256 MB cache keeps most of them
-//    from one application to the next), a solve's operator and vectors up to
-//    256 MiB (24^3, N = 7, FP32 flexible CG at 314 MB: 137 ms a solve with the
-//    streaming forms, 152 ms with these): no streaming hints, which would make the next application miss
-//    (FP64 N = 7, 4M nodes 43.4 -> 37.9 us; FP32 N = 7, 8M nodes 39.5 -> 34.4;
+//    256 MiB of what one application of the standalone operator moves, or of
+//    a solve's operator and vectors (24^3, N = 7, FP32 flexible CG at 314 MB:
+//    137 ms a solve with the streaming forms, 152 ms with these): no streaming
+//    hints, which would make the next application miss (FP64 N = 7, 4M nodes
+//    44.3 -> 40.7 us, 5.2M nodes 58.2 -> 63.4; FP32 N = 7, 8M nodes 40.6 -> 38.1;
 //    BF16 N = 1, 2M nodes 20.1 -> 6.4), and in the solvers element blocks
 //    numbered so that every XCD takes one contiguous run of them (XCD):
 //    neighbours share the gathered vector's lines in one L2 (FP64 N = 6, 2.4M
@@ -85,7 +85,7 @@ template <int N1, class TC = double> constexpr int lds_words(int epb) {
 // (FP64 at n1 = 7 and 9, where the unpredicated loads were 5-7 % slower;
 // elsewhere they are faster, by 12 % at n1 = 2 and 16 % at n1 = 3).
 constexpr int64_t AX_SMALL_NODES = 200000;
-constexpr double AX_CACHE_BYTES = 320.0 * 1024 * 1024;
+constexpr double AX_CACHE_BYTES = 256.0 * 1024 * 1024;
 constexpr double SOLVE_CACHE_BYTES = 256.0 * 1024 * 1024;
 
 // standalone operator; node_bytes: what one application moves per local node

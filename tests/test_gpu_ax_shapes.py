@@ -40,7 +40,7 @@ def _reference(G, D, u):
 
 
 # local nodes of the size classes by precision (bytes per node 64, 32, 18;
-# 320 MiB): just above 0.2M, and beyond the cache
+# 256 MiB): just above 0.2M, and beyond the cache
 SIZES = [(N, prec, nodes)
          for N in range(1, 9)
          for prec, nodes in [("fp64", 2.1e5), ("fp32", 2.1e5), ("bf16", 2.1e5),
