@@ -8,8 +8,8 @@
 // The paper's kernel reads its 4r + 1 neighbours straight from memory, one
 // node per work-item.  HBM-bound on MI355X (24 bytes per node: u_cur and
 // u_prev read, u_next written), the kernel here reads every value once:
-//   * a workgroup owns a strip of FD_TX columns (one thread per column) and a
-//     chunk of rows, and marches down the chunk FD_P rows at a time;
+//   * a workgroup owns a strip of TX columns (one thread per column) and a
+//     chunk of ROWS rows, and marches down the chunk FD_P rows at a time;
 //   * each thread keeps the 2r + FD_P values of its column that the
 //     y-stencil of the current rows needs in registers (a sliding window:
 //     each new row is one load);
@@ -18,11 +18,10 @@
 //     barrier per FD_P rows);
 //   * the loads of the next FD_P rows are issued before the current rows are
 //     computed, so every wave keeps loads in flight across the barrier;
-//   * short row chunks (16 rows for r <= 2, 32 otherwise; timed on 8192^2)
-//     give many workgroups, which a stream of two reads and one write needs
-//     to approach the bandwidth a plain copy reaches (a flat
+//   * short row chunks give many workgroups, which a stream of two reads and
+//     one write needs to approach the bandwidth a plain copy reaches (a flat
 //     2-read-1-write kernel reaches 75 % of peak here), at the price of
-//     re-reading 2r rows per chunk from cache;
+//     re-reading 2r rows per chunk from cache; fd_shape has the sizes;
 //   * blocks are numbered row-major over (strip, chunk): workgroups are
 //     dealt to the 8 XCDs round-robin, so with a multiple of 8 strips each
 //     XCD takes every eighth strip across the grid's width, row chunk after
@@ -36,11 +35,32 @@
 
 namespace sem {
 
-constexpr int FD_TX = 256;  // columns per workgroup (four waves)
-constexpr int FD_P = 4;     // rows per pipeline step
+constexpr int FD_P = 4;  // rows per pipeline step
 constexpr int FD_RMAX = 7;
-// rows per workgroup (a multiple of FD_P)
-template <int R> constexpr int fd_rows() { return R <= 2 ? 16 : 32; }
+
+// Columns and rows of a workgroup.  Timed over 128^2 to 9001 x 8003 nodes and
+// every r, us per step against strips of 256 x 16 (r <= 2) or x 32 rows:
+//   * 64 x 4 up to 0.7M nodes: a small grid spreads over the compute units
+//     and a workgroup's serial march is one pipeline step (r = 7, 245 x 197
+//     19.8 -> 6.2, 700^2 22.8 -> 9.7; r = 1, 700^2 9.2 -> 6.4; at 1024^2
+//     256 x 8 is already 7 % faster for r = 7);
+//   * 256 x 8 up to 6M nodes (r = 7, 1024^2 21.1 -> 10.7, 2048^2 32.1 -> 27.0;
+//     r = 4, 2048^2 27.3 -> 21.7), and beyond 12M for r <= 3, where re-reading
+//     2r rows per chunk costs less than the extra workgroups give (8192^2:
+//     r = 1, 2, 3 261, 265, 268 -> 252, 253, 259; r = 4 273 -> 274, r = 7 329 ->
+//     358);
+//   * 256 x 16 between (3000^2: r = 3..7 44.5, 45.8, 50.5, 52.3, 59.0 -> 42.5,
+//     44.6, 48.0, 49.2, 54.1; x 8 is slower for r = 2, 40.2 -> 42.2);
+//   * 256 x 32 for r >= 4 beyond 12M nodes.
+struct FdShape {
+  int tx, rows;
+};
+static FdShape fd_shape(double nodes, int r) {
+  if (nodes <= 700000) return {64, 4};
+  if (nodes <= 6000000) return {256, 8};
+  if (nodes <= 12000000) return {256, 16};
+  return {256, r <= 3 ? 8 : 32};
+}
 
 struct FdArgs {
   const double *u_cur, *u_prev;
@@ -59,19 +79,19 @@ __device__ inline int64_t fd_wrap(int64_t v, int64_t n) {
   return v;
 }
 
-template <int R>
-__global__ void __launch_bounds__(FD_TX) k_fd2d(FdArgs a) {
+template <int R, int TX, int ROWS>
+__global__ void __launch_bounds__(TX) k_fd2d(FdArgs a) {
   // separate multiplies and adds in the stated order (no fused
   // multiply-add): at 24 bytes per node the kernel is bound by HBM, not by
   // the ~8r flops, and the update is then reproducible bit for bit
 #pragma clang fp contract(off)
-  constexpr int P = FD_P, Q = 2 * R + P, LW = FD_TX + 2 * R, ROWS = fd_rows<R>();
+  constexpr int P = FD_P, Q = 2 * R + P, LW = TX + 2 * R;
   __shared__ double rows[2][P][LW];
   const int tx = threadIdx.x;
   const int64_t nx = a.nx, ny = a.ny;
   // 32-bit decode of the block index (the grid has < 2^31 blocks)
   const uint32_t by = blockIdx.x / a.gx, bx = blockIdx.x - by * a.gx;
-  const int64_t i0 = (int64_t)bx * FD_TX;
+  const int64_t i0 = (int64_t)bx * TX;
   const int64_t j0 = (int64_t)by * ROWS;
   const int64_t jend = j0 + ROWS < ny ? j0 + ROWS : ny;
   const bool act = i0 + tx < nx;
@@ -84,7 +104,7 @@ __global__ void __launch_bounds__(FD_TX) k_fd2d(FdArgs a) {
   };
   const int64_t ci = wrap_col(i0 + tx);
   const int64_t cl = tx < R ? wrap_col(i0 - R + tx) : 0;
-  const int64_t cr = tx < R ? wrap_col(i0 + FD_TX + tx) : 0;
+  const int64_t cr = tx < R ? wrap_col(i0 + TX + tx) : 0;
   const double *uc = a.u_cur;
 
   // q[m] holds u_cur(ci, j - R + m) for the current first row j
@@ -120,7 +140,7 @@ __global__ void __launch_bounds__(FD_TX) k_fd2d(FdArgs a) {
       rows[buf][p][R + tx] = q[R + p];
       if (tx < R) {
         rows[buf][p][tx] = hl[p];
-        rows[buf][p][R + FD_TX + tx] = hr[p];
+        rows[buf][p][R + TX + tx] = hr[p];
       }
     }
     if (j + P < jend) issue(j + P);  // in flight during this step
@@ -179,8 +199,8 @@ void launch_fd2d(const double *u_cur, const double *u_prev, double *u_next,
   if (nx < 1 || ny < 1) fail(SEM_ERR_ARG, "fd2d: grid must have nx, ny >= 1");
   if (!u_cur || !u_prev || !u_next) fail(SEM_ERR_ARG, "fd2d: null buffer");
   if (u_next == u_cur) fail(SEM_ERR_ARG, "fd2d: u_next must not alias u_cur");
-  const int rows = r <= 2 ? 16 : 32;  // fd_rows<r>()
-  const int64_t gx = (nx + FD_TX - 1) / FD_TX, gy = (ny + rows - 1) / rows;
+  const FdShape sh = fd_shape((double)nx * (double)ny, r);
+  const int64_t gx = (nx + sh.tx - 1) / sh.tx, gy = (ny + sh.rows - 1) / sh.rows;
   if (gx * gy > INT32_MAX) fail(SEM_ERR_ARG, "fd2d: grid too large");
   FdArgs a{};
   a.u_cur = u_cur;
@@ -191,11 +211,18 @@ void launch_fd2d(const double *u_cur, const double *u_prev, double *u_next,
   a.gx = (uint32_t)gx;
   a.c = c;
   fd2d_weights_host(r, a.w);
-  const dim3 grid((unsigned)(gx * gy)), block(FD_TX);
+  const dim3 grid((unsigned)(gx * gy)), block(sh.tx);
   switch (r) {
 #define SEM_FD(RR)                                                    \
   case RR:                                                            \
-    hipLaunchKernelGGL(k_fd2d<RR>, grid, block, 0, s, a);             \
+    if (sh.tx == 64)                                                  \
+      hipLaunchKernelGGL((k_fd2d<RR, 64, 4>), grid, block, 0, s, a);  \
+    else if (sh.rows == 8)                                            \
+      hipLaunchKernelGGL((k_fd2d<RR, 256, 8>), grid, block, 0, s, a); \
+    else if (sh.rows == 16)                                           \
+      hipLaunchKernelGGL((k_fd2d<RR, 256, 16>), grid, block, 0, s, a); \
+    else                                                              \
+      hipLaunchKernelGGL((k_fd2d<RR, 256, 32>), grid, block, 0, s, a); \
     break;
     SEM_FD(1)
     SEM_FD(2)
