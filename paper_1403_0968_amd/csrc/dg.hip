@@ -45,7 +45,7 @@ namespace sem {
 
 typedef double dg_d4 __attribute__((ext_vector_type(4)));
 
-constexpr int DG_WAVES = 4;  // waves per workgroup, 16 elements each
+constexpr int DG_WAVES = 4;  // most waves per workgroup, 16 elements each
 
 template <int N> struct DgShape {
   static constexpr int NP = (N + 1) * (N + 2) / 2;
@@ -70,7 +70,7 @@ __global__ void __launch_bounds__(64 * DG_WAVES)
   constexpr int NP = S::NP, NT = S::NT, NK = S::NK;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = lane & 15, kq = lane >> 4;
-  const int64_t blk = (int64_t)blockIdx.x * DG_WAVES + wave;
+  const int64_t blk = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;
   const int64_t e = blk * 16 + col;
   const bool act = e < E;
   // a wave past the last block has nothing to do (no barrier in this kernel)
@@ -174,17 +174,25 @@ __global__ void __launch_bounds__(64 * DG_WAVES)
 template <int N>
 static void launch_n(const dg_handle *h, const double *Q, double *rhs, bool blocked,
                      hipStream_t s) {
-  const int64_t per = 16 * DG_WAVES;
+  // The waves of a workgroup share nothing.  One wave per workgroup spreads a
+  // mesh of a few waves per compute unit evenly (20,000 triangles, N = 5, 7, 8:
+  // 10.0, 16.8, 20.7 -> 9.4, 15.9, 19.6 us; element-major 11.6, 20.7, 25.7 ->
+  // 10.6, 18.1, 22.9) and is no slower on large ones in blocks (212,800, N = 5,
+  // 7, 8: 56.1, 106.5, 140 -> 54.7, 105, 139); element-major, where neighbouring
+  // waves share lines, four are up to 2 % faster beyond 32768 (64,800, N = 4:
+  // 14.1 -> 13.9).
+  const int waves = blocked || h->E <= 32768 ? 1 : DG_WAVES;
+  const int64_t per = 16 * waves;
   const int64_t blocks = (h->E + per - 1) / per;
   if (blocks == 0) return;
   if (blocked)
     hipLaunchKernelGGL((k_dg_volume<N, true>), dim3((unsigned)blocks),
-                       dim3(64 * DG_WAVES), 0, s, h->E, Q, rhs, h->geo.as<double>(),
+                       dim3(64 * waves), 0, s, h->E, Q, rhs, h->geo.as<double>(),
                        h->dBb.as<double>(), h->Drw.as<double>(),
                        h->Dsw.as<double>(), h->g);
   else
     hipLaunchKernelGGL((k_dg_volume<N, false>), dim3((unsigned)blocks),
-                       dim3(64 * DG_WAVES), 0, s, h->E, Q, rhs, h->geo.as<double>(),
+                       dim3(64 * waves), 0, s, h->E, Q, rhs, h->geo.as<double>(),
                        h->dB.as<double>(), h->Drw.as<double>(),
                        h->Dsw.as<double>(), h->g);
 }
