@@ -59,8 +59,8 @@ template <int N> struct DgShape {
 // elements x 32 bytes.  BLK = true: blocks of 16 elements, [E/16][3][Np][16]
 // and [E/16][2][Np][16] (element fastest), so each of them is 512
 // contiguous bytes.
-template <int N, bool BLK>
-__global__ void __launch_bounds__(64 * DG_WAVES)
+template <int N, bool BLK, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES)
     __attribute__((amdgpu_waves_per_eu(DgShape<N>::WAVES_PER_EU)))
     k_dg_volume(int64_t E, const double *__restrict__ Q, double *__restrict__ rhs,
                 const double *__restrict__ geo, const double *__restrict__ dB,
@@ -70,7 +70,7 @@ __global__ void __launch_bounds__(64 * DG_WAVES)
   constexpr int NP = S::NP, NT = S::NT, NK = S::NK;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = lane & 15, kq = lane >> 4;
-  const int64_t blk = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;
+  const int64_t blk = (int64_t)blockIdx.x * WAVES + wave;
   const int64_t e = blk * 16 + col;
   const bool act = e < E;
   // a wave past the last block has nothing to do (no barrier in this kernel)
@@ -185,15 +185,18 @@ static void launch_n(const dg_handle *h, const double *Q, double *rhs, bool bloc
   const int64_t per = 16 * waves;
   const int64_t blocks = (h->E + per - 1) / per;
   if (blocks == 0) return;
+  const dim3 grid((unsigned)blocks), block(64 * waves);
   if (blocked)
-    hipLaunchKernelGGL((k_dg_volume<N, true>), dim3((unsigned)blocks),
-                       dim3(64 * waves), 0, s, h->E, Q, rhs, h->geo.as<double>(),
-                       h->dBb.as<double>(), h->Drw.as<double>(),
+    hipLaunchKernelGGL((k_dg_volume<N, true, 1>), grid, block, 0, s, h->E, Q, rhs,
+                       h->geo.as<double>(), h->dBb.as<double>(), h->Drw.as<double>(),
+                       h->Dsw.as<double>(), h->g);
+  else if (waves == 1)
+    hipLaunchKernelGGL((k_dg_volume<N, false, 1>), grid, block, 0, s, h->E, Q, rhs,
+                       h->geo.as<double>(), h->dB.as<double>(), h->Drw.as<double>(),
                        h->Dsw.as<double>(), h->g);
   else
-    hipLaunchKernelGGL((k_dg_volume<N, false>), dim3((unsigned)blocks),
-                       dim3(64 * waves), 0, s, h->E, Q, rhs, h->geo.as<double>(),
-                       h->dB.as<double>(), h->Drw.as<double>(),
+    hipLaunchKernelGGL((k_dg_volume<N, false, DG_WAVES>), grid, block, 0, s, h->E, Q, rhs,
+                       h->geo.as<double>(), h->dB.as<double>(), h->Drw.as<double>(),
                        h->Dsw.as<double>(), h->g);
 }
 
