@@ -667,7 +667,7 @@ __device__ inline void solve_elem_mfma(int l, MfmaLdsSplit &L, int64_t e, bool a
   }
   const int i = l & 7, j = l >> 3;
   double cd = 0.0;
-  if (i < N1 && j < N1) {
+  if (act && i < N1 && j < N1) {  // (wval reads H at the element)
 #pragma unroll
     for (int t = 0; t < N1; ++t) cd += (double)pv[t] * (double)wval(i, j, t);
   }
@@ -781,11 +781,12 @@ __device__ inline void solve_elem_mfma9(int l, MfmaLds9 &L, int64_t e, bool act,
   if (act) {
     for (int p = l; p < E9; p += 64) w[e * E9 + p] = wval(p);
   }
-  // each lane's nodes in ascending t, then the lanes
+  // each lane's nodes in ascending t, then the lanes (wval reads H at the
+  // element)
   double cd = 0.0;
 #pragma unroll
   for (int t = 0; t < T9; ++t)
-    if (l + 64 * t < E9) cd += (double)pv[t] * (double)wval(l + 64 * t);
+    if (act && l + 64 * t < E9) cd += (double)pv[t] * (double)wval(l + 64 * t);
   cd = wave_sum(cd);
   if (act && l == 0) edot[e] = cd;
 }
