@@ -615,7 +615,7 @@ __device__ inline void gather_dir(const Box &box, const DirMfma &d, bool act, in
   }
 #pragma unroll
   for (int t = 0; t < NT; ++t)
-    if (!d.first) v[t] = v[t] + d.beta * po[t];
+    if (!d.first) v[t] = axpy1(d.beta, po[t], v[t]);
 #pragma unroll
   for (int t = 0; t < NT; ++t)
     if (own[t]) d.pnew[g[t]] = v[t];

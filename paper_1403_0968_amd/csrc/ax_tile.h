@@ -320,7 +320,7 @@ __device__ __forceinline__ void ax_tile(int t, int64_t e0, int64_t E,
 #pragma unroll
     for (int k = 0; k < N1; ++k) {
       // the first iteration has no old direction (its buffer may hold anything)
-      if (!ds.first) ucol[k] = ucol[k] + beta * pcol[k];
+      if (!ds.first) ucol[k] = axpy1(beta, pcol[k], ucol[k]);
     }
     if (own_c) {
       const gp<TU> pn = (gp<TU>)dir->pnew;

@@ -145,6 +145,14 @@ __device__ inline DirStep dir_step(CgState *st, const DirScalars &s, const DirPa
   return {beta, s.ready == 2, done != 0};
 }
 
+// a x + y rounded once.  The vector updates of the iteration are written with
+// it: left to the compiler, the product z + beta p was contracted in one kernel
+// and, moved into the branch that loads p, rounded by itself in another, and a
+// solve's bits depended on the kernel (matrix-core refinement at N = 1, 2,
+// alone against in a batch).
+__device__ inline double axpy1(double a, double x, double y) { return __builtin_fma(a, x, y); }
+__device__ inline float axpy1(float a, float x, float y) { return __builtin_fmaf(a, x, y); }
+
 // whether an element at c stores the value of its node (i, j, k): the first
 // element along each direction does (the coordinate that wraps to 0 belongs
 // to element 0)

@@ -351,8 +351,8 @@ __device__ __forceinline__ void xr_asm_chunk(const Box &bx, const XrVecs<TV, TD>
     for (int k = 0; k < K; ++k) {
       const int64_t g = g0 + k * RT;
       if (WHOLE || g < end) {
-        if constexpr (FUSED) a.x[g] = xv[k] + al * pv[k];
-        const TV rn = rv[k] - al * sw[k];
+        if constexpr (FUSED) a.x[g] = axpy1(al, pv[k], xv[k]);
+        const TV rn = axpy1(-al, sw[k], rv[k]);
         st_h<NT>(rn, a.r + g);
         const TV zn = (TV)(dv[k] * rn);
         a.z[g] = zn;
@@ -489,17 +489,17 @@ __device__ __forceinline__ void p_chunk(gp<const TV> z, gp<TV> p, gp<TV> x, TV a
     }
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-      st_h<true>(xv[k] + alpha * pv[k], x + g0 + k * RT);
-      p[g0 + k * RT] = zv[k] + beta * pv[k];
+      st_h<true>(axpy1(alpha, pv[k], xv[k]), x + g0 + k * RT);
+      p[g0 + k * RT] = axpy1(beta, pv[k], zv[k]);
     }
   } else if (run) {
     for (int64_t g = g0; g < end; g += RT) {
       const TV pv = p[g];
-      x[g] = x[g] + alpha * pv;
-      p[g] = z[g] + beta * pv;
+      x[g] = axpy1(alpha, pv, x[g]);
+      p[g] = axpy1(beta, pv, z[g]);
     }
   } else {
-    for (int64_t g = g0; g < end; g += RT) x[g] = x[g] + alpha * p[g];
+    for (int64_t g = g0; g < end; g += RT) x[g] = axpy1(alpha, p[g], x[g]);
   }
 }
 
