@@ -689,8 +689,10 @@ __device__ inline bool batch_dir_mfma(const BatchSolve &sd, CgState *st, const B
   return dir_mfma(st + it.solve, bd.mode, bd.part, bd.stride, beg, end, writer, dir);
 }
 
+// (three waves per SIMD are what the workgroups' LDS allows: without the hint
+// N = 6 took the registers of two)
 template <int N1, bool SPLIT>
-__global__ void __launch_bounds__(64 * MW)
+__global__ void __launch_bounds__(64 * MW) __attribute__((amdgpu_waves_per_eu(3)))
     k_bax_mfma(const BatchSolve *__restrict__ sds, CgState *st,
                const AxItem *__restrict__ items, int nitems, int epb, BaxDir bd) {
   __shared__ MfmaLdsSplit lds[MW];
@@ -794,7 +796,7 @@ __device__ inline void solve_elem_mfma9(int l, MfmaLds9 &L, int64_t e, bool act,
 // the batched solver operator at n1 = 9: as k_bax_mfma, MW9 elements per
 // workgroup pass
 template <bool SPLIT>
-__global__ void __launch_bounds__(64 * MW9)
+__global__ void __launch_bounds__(64 * MW9) __attribute__((amdgpu_waves_per_eu(2)))
     k_bax_mfma9(const BatchSolve *__restrict__ sds, CgState *st,
                 const AxItem *__restrict__ items, int nitems, int epb, BaxDir bd) {
   __shared__ MfmaLds9 lds[MW9];
@@ -810,8 +812,14 @@ __global__ void __launch_bounds__(64 * MW9)
                 bh, bl);
     for (int e0 = 0; e0 < epb; e0 += MW9) {  // uniform per block
       const int64_t e = it.elem0 + e0 + wv;
+      // the lane number by a value the compiler cannot see through: it moved the
+      // element routine's lane addresses and masks out of this loop, which took
+      // 280 registers, one wave per SIMD (8 refinements of 9^3, N = 8, 96
+      // iterations: 24.1 -> 16.7 ms)
+      int le = l;
+      asm volatile("" : "+v"(le));
       solve_elem_mfma9<SPLIT>(
-          l, L, e, e0 + wv < epb && e < sd.E, sd.box, dir, (gp<float>)sd.v32[VWL],
+          le, L, e, e0 + wv < epb && e < sd.E, sd.box, dir, (gp<float>)sd.v32[VWL],
           (const uint16_t *)sd.G16, (gp<const uint16_t>)sd.H16, fh, fl, bh, bl,
           (gp<double>)sd.edot);
       wave_lds_sync();  // L is reused by the next element
