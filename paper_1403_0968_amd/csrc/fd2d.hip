@@ -52,14 +52,25 @@ constexpr int FD_RMAX = 7;
 //   * 256 x 16 between (3000^2: r = 3..7 44.5, 45.8, 50.5, 52.3, 59.0 -> 42.5,
 //     44.6, 48.0, 49.2, 54.1; x 8 is slower for r = 2, 40.2 -> 42.2);
 //   * 256 x 32 for r >= 4 beyond 12M nodes.
+// A launch holds fewer than 2^32 threads (more are dropped without an error):
+// a tall, narrow grid whose small chunks would be more takes 256 x 32.
+constexpr double FD_MAX_THREADS = 4294967295.0;
 struct FdShape {
   int tx, rows;
 };
-static FdShape fd_shape(double nodes, int r) {
-  if (nodes <= 700000) return {64, 4};
-  if (nodes <= 6000000) return {256, 8};
-  if (nodes <= 12000000) return {256, 16};
-  return {256, r <= 3 ? 8 : 32};
+static double fd_threads(int64_t nx, int64_t ny, const FdShape &sh) {
+  return (double)((nx + sh.tx - 1) / sh.tx) * (double)((ny + sh.rows - 1) / sh.rows) * sh.tx;
+}
+static FdShape fd_shape(int64_t nx, int64_t ny, int r) {
+  const double nodes = (double)nx * (double)ny;
+  FdShape sh = {256, r <= 3 ? 8 : 32};
+  if (nodes <= 700000)
+    sh = {64, 4};
+  else if (nodes <= 6000000)
+    sh = {256, 8};
+  else if (nodes <= 12000000)
+    sh = {256, 16};
+  return fd_threads(nx, ny, sh) <= FD_MAX_THREADS ? sh : FdShape{256, 32};
 }
 
 struct FdArgs {
@@ -199,9 +210,9 @@ void launch_fd2d(const double *u_cur, const double *u_prev, double *u_next,
   if (nx < 1 || ny < 1) fail(SEM_ERR_ARG, "fd2d: grid must have nx, ny >= 1");
   if (!u_cur || !u_prev || !u_next) fail(SEM_ERR_ARG, "fd2d: null buffer");
   if (u_next == u_cur) fail(SEM_ERR_ARG, "fd2d: u_next must not alias u_cur");
-  const FdShape sh = fd_shape((double)nx * (double)ny, r);
+  const FdShape sh = fd_shape(nx, ny, r);
+  if (fd_threads(nx, ny, sh) > FD_MAX_THREADS) fail(SEM_ERR_ARG, "fd2d: grid too large");
   const int64_t gx = (nx + sh.tx - 1) / sh.tx, gy = (ny + sh.rows - 1) / sh.rows;
-  if (gx * gy > INT32_MAX) fail(SEM_ERR_ARG, "fd2d: grid too large");
   FdArgs a{};
   a.u_cur = u_cur;
   a.u_prev = u_prev;
