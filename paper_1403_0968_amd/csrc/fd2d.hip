@@ -38,20 +38,27 @@ namespace sem {
 constexpr int FD_P = 4;  // rows per pipeline step
 constexpr int FD_RMAX = 7;
 
-// Columns and rows of a workgroup.  Timed over 128^2 to 9001 x 8003 nodes and
-// every r, us per step against strips of 256 x 16 (r <= 2) or x 32 rows:
-//   * 64 x 4 up to 0.7M nodes: a small grid spreads over the compute units
-//     and a workgroup's serial march is one pipeline step (r = 7, 245 x 197
-//     19.8 -> 6.2, 700^2 22.8 -> 9.7; r = 1, 700^2 9.2 -> 6.4; at 1024^2
-//     256 x 8 is already 7 % faster for r = 7);
-//   * 256 x 8 up to 6M nodes (r = 7, 1024^2 21.1 -> 10.7, 2048^2 32.1 -> 27.0;
-//     r = 4, 2048^2 27.3 -> 21.7), and beyond 12M for r <= 3, where re-reading
-//     2r rows per chunk costs less than the extra workgroups give (8192^2:
-//     r = 1, 2, 3 261, 265, 268 -> 252, 253, 259; r = 4 273 -> 274, r = 7 329 ->
-//     358);
-//   * 256 x 16 between (3000^2: r = 3..7 44.5, 45.8, 50.5, 52.3, 59.0 -> 42.5,
-//     44.6, 48.0, 49.2, 54.1; x 8 is slower for r = 2, 40.2 -> 42.2);
-//   * 256 x 32 for r >= 4 beyond 12M nodes.
+// Columns and rows of a workgroup, by the grid's sides.  Timed over 230 grids
+// of 128^2 to 73M nodes, 1 to 21M on a side, and every r, us per step; before:
+// strips of 256 x 16 (r <= 2) or x 32 rows.
+//   * 64 x 4 on grids up to 64 wide, where wider strips idle (40 x 10^6,
+//     r = 3 453 -> 267; 1 x 15M 5841 -> 3151), and up to 0.7M nodes: a small
+//     grid spreads over the compute units and a workgroup's serial march is one
+//     pipeline step (r = 7, 245 x 197 19.8 -> 6.2, 700^2 22.8 -> 9.7);
+//   * 256 x 8 up to 1.5M nodes, and up to 3M threads (r <= 2: 2.5M) where the
+//     grid is at least 64 tall (r = 7, 1024^2 23.4 -> 10.2, 1500^2 27.3 -> 21.1;
+//     187500 x 16 is slower with it, 20.4 -> 23.0);
+//   * 256 x 8 on larger grids for r <= 4 where the strips are a multiple of 8:
+//     a strip's chunks then run on one XCD, whose L2 holds the 2r rows that
+//     chunks share (8192^2, r = 1, 2, 3, 4 263, 263, 267, 270 -> 259, 256, 257,
+//     265, 16384 x 1024, r = 3 78 -> 64; 20 strips, 5000 x 3000 60, 62, 65, 67
+//     -> 62, 66, 70, 73);
+//   * 256 x 16 up to 5.2M threads from 32 rows, and up to 12M nodes from
+//     1024 x 512 (3000^2, r = 3, 5, 7 42.8, 49.1, 58.9 -> 41.3, 46.3, 55.8;
+//     80000 x 100, r = 7 is slower with it, 44.3 -> 47.4);
+//   * otherwise 256 x 16 (r <= 2) or 256 x 32, beyond 50M nodes a step shorter
+//     for r <= 4 (5000 x 13000, r = 1, 2, 3, 4 278, 278, 290, 291 -> 265, 269,
+//     278, 281; at 30000 x 1000 slower, 114, 118, 117, 121 -> 115, 122, 122, 126).
 // A launch holds fewer than 2^32 threads (more are dropped without an error):
 // a tall, narrow grid whose small chunks would be more takes 256 x 32.
 constexpr double FD_MAX_THREADS = 4294967295.0;
@@ -63,12 +70,17 @@ static double fd_threads(int64_t nx, int64_t ny, const FdShape &sh) {
 }
 static FdShape fd_shape(int64_t nx, int64_t ny, int r) {
   const double nodes = (double)nx * (double)ny;
-  FdShape sh = {256, r <= 3 ? 8 : 32};
-  if (nodes <= 700000)
+  const int64_t strips = (nx + 255) / 256;
+  const double threads = 256.0 * (double)strips * (double)ny;
+  const bool large = nodes > 5e7;
+  FdShape sh = {256, r <= 2 ? (large ? 8 : 16) : large && r <= 4 ? 16 : 32};
+  if (nx <= 64 || nodes <= 700000)
     sh = {64, 4};
-  else if (nodes <= 6000000)
+  else if (nodes <= 1500000 || (r <= 4 && strips % 8 == 0 && ny >= 512) ||
+           (ny >= 64 && threads <= (r <= 2 ? 2500000 : 3000000)))
     sh = {256, 8};
-  else if (nodes <= 12000000)
+  else if ((ny >= 32 && threads <= 5200000) ||
+           (nx >= 1024 && ny >= 512 && nodes <= 12000000))
     sh = {256, 16};
   return fd_threads(nx, ny, sh) <= FD_MAX_THREADS ? sh : FdShape{256, 32};
 }
