@@ -27,6 +27,7 @@
 // same data and run side by side: 68 us a pass, against 680 us with a launch
 // per product, a thread per bias (walking the batch) and a thread per sample
 // in the loss.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -579,8 +580,8 @@ static void forward_into(sem_mlp *net, const uint16_t *X, int ldx, int B, float 
   const float *W3 = b2 + H;
   const float *b3 = W3 + (int64_t)net->n_out * H;
   if (keep || net->prec == SEM_FP32) ensure_scratch(net, B);
-  const unsigned gm = (unsigned)((B + 15) / 16);
   if (net->prec == SEM_FP32) {
+    const unsigned gm = (unsigned)((B + 15) / 16);
     float *h1f = net->h1f.as<float>(), *h2f = net->h2f.as<float>();
     hipLaunchKernelGGL((k_dense_f32<uint16_t, true>), dim3(gm, H / 16), dim3(256),
                        0, s, B, net->n_in, H, X, ldx, W1, net->n_in, b1, h1f, H);
@@ -593,13 +594,18 @@ static void forward_into(sem_mlp *net, const uint16_t *X, int ldx, int B, float 
     SEM_HIP(hipGetLastError());
     return;
   }
-  hipLaunchKernelGGL(k_forward_mfma, dim3(gm), dim3(64 * FW_WAVES), 0, s, B, net->kin,
-                     net->n_out, X, ldx, net->W1b.as<uint16_t>(), b1,
-                     net->W2b.as<uint16_t>(), b2, net->W3b.as<uint16_t>(), b3, O, ldo,
-                     keep ? net->h1b.as<uint16_t>() : nullptr,
-                     keep ? net->h2b.as<uint16_t>() : nullptr,
-                     keep ? net->h1f.as<float>() : nullptr,
-                     keep ? net->h2f.as<float>() : nullptr);
+  // (a launch holds fewer than 2^32 threads, here 32 a sample)
+  constexpr int ROWS = 1 << 26;
+  auto kept = [&](auto *p, int64_t r0) { return keep ? p + r0 * H : nullptr; };
+  for (int64_t r0 = 0; r0 < B; r0 += ROWS) {
+    const int n = (int)std::min<int64_t>(B - r0, ROWS);
+    hipLaunchKernelGGL(k_forward_mfma, dim3((unsigned)((n + 15) / 16)), dim3(64 * FW_WAVES), 0,
+                       s, n, net->kin, net->n_out, X + r0 * ldx, ldx, net->W1b.as<uint16_t>(),
+                       b1, net->W2b.as<uint16_t>(), b2, net->W3b.as<uint16_t>(), b3,
+                       O + r0 * ldo, ldo, kept(net->h1b.as<uint16_t>(), r0),
+                       kept(net->h2b.as<uint16_t>(), r0), kept(net->h1f.as<float>(), r0),
+                       kept(net->h2f.as<float>(), r0));
+  }
   SEM_HIP(hipGetLastError());
 }
 
