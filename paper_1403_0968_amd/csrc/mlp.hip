@@ -609,9 +609,22 @@ static void forward_into(sem_mlp *net, const uint16_t *X, int ldx, int B, float 
   SEM_HIP(hipGetLastError());
 }
 
+// whether an output of n floats at p lies over the samples X [B][ldx]
+static bool over_input(const float *p, int64_t n, const uint16_t *X, int ldx, int B) {
+  const uintptr_t a = (uintptr_t)p, x = (uintptr_t)X;
+  return a < x + (uintptr_t)((int64_t)B * ldx * 2) && x < a + (uintptr_t)(n * 4);
+}
+
 void mlp_forward(sem_mlp *net, const uint16_t *X, int ldx, int B, float *O,
                  int ldo, hipStream_t s) {
-  forward_into(net, X, ldx, B, O, ldo, false, s);
+  if (B <= 0 || !over_input(O, (int64_t)B * ldo, X, ldx, B))
+    return forward_into(net, X, ldx, B, O, ldo, false, s);
+  // in place: workgroups store their samples' outputs while others still read
+  // theirs, so the outputs take the way through the scratch
+  ensure_scratch(net, B);
+  float *of = net->of.as<float>();
+  forward_into(net, X, ldx, B, of, ldo, false, s);
+  SEM_HIP(hipMemcpyAsync(O, of, (size_t)B * ldo * 4, hipMemcpyDeviceToDevice, s));
 }
 
 // Backward pass from net->dO (written by a loss kernel) into net->grad
@@ -681,6 +694,11 @@ double mlp_loss_grad_factor(sem_mlp *net, const uint16_t *X, int ldx,
                       "n_out = K(K+1)/2");
   ensure_scratch(net, B);
   const int wo = net->n_out > 16 ? net->n_out : 16;
+  // a gradient that lies over X, which the last layer's launch still reads, is
+  // copied after it
+  const bool over = grad && over_input(grad, net->np, X, ldx, B);
+  float *copy = over ? grad : nullptr;
+  if (over) grad = nullptr;
   forward_into(net, X, ldx, B, net->of.as<float>(), wo, true, s);
   const dim3 g((unsigned)((B + LF_WAVES - 1) / LF_WAVES)), t(64 * LF_WAVES);
   if (K == 1)
@@ -693,8 +711,12 @@ double mlp_loss_grad_factor(sem_mlp *net, const uint16_t *X, int ldx,
     hipLaunchKernelGGL(k_loss_factor<27>, g, t, 0, s, B, net->of.as<float>(), wo, T,
                        net->dO.as<float>(), wo, net->lossp.as<double>());
   SEM_HIP(hipGetLastError());
-  return net->prec == SEM_FP32 ? mlp_backward<float>(net, X, ldx, B, K, grad, s)
-                               : mlp_backward<uint16_t>(net, X, ldx, B, K, grad, s);
+  const double loss = net->prec == SEM_FP32
+                          ? mlp_backward<float>(net, X, ldx, B, K, grad, s)
+                          : mlp_backward<uint16_t>(net, X, ldx, B, K, grad, s);
+  if (copy)
+    SEM_HIP(hipMemcpyAsync(copy, net->grad.p, (size_t)net->np * 4, hipMemcpyDeviceToDevice, s));
+  return loss;
 }
 
 uint64_t mlp_version(const sem_mlp *net) { return net->version; }
