@@ -907,6 +907,7 @@ struct sem_batch {
   hipEvent_t ev0 = nullptr, ev1 = nullptr, fence = nullptr;
   struct GraphEntry {
     int prec, k, jac, mode, par, ver;  // ver: list version (0: the full lists)
+    int par_out;                       // the direction buffers after its launch
     hipGraphExec_t exec;
   };
   // snapshot recording of solve 0 (training data), FP64 unique vectors
@@ -1469,17 +1470,19 @@ static void upload_active(sem_batch *b, const std::vector<int> &act,
   SEM_HIP(hipStreamSynchronize(b->s));
 }
 
-static hipGraphExec_t get_graph(sem_batch *b, int prec, int K, int jac,
-                                int mode) {
+static const sem_batch::GraphEntry &get_graph(sem_batch *b, int prec, int K, int jac,
+                                              int mode) {
   const int ver = b->compact ? b->list_ver : 0, par = b->par;
   for (auto &g : b->graphs)
     if (g.prec == prec && g.k == K && g.jac == jac && g.mode == mode && g.par == par &&
         g.ver == ver)
-      return g.exec;
+      return g;
   hipGraph_t graph;
+  int par_out = par;
   SEM_HIP(hipStreamBeginCapture(b->s, hipStreamCaptureModeThreadLocal));
   try {
     iterations(b, prec, K, jac, mode);
+    par_out = b->par;
     b->par = par;  // nothing has run yet
   } catch (...) {
     b->par = par;
@@ -1491,8 +1494,8 @@ static hipGraphExec_t get_graph(sem_batch *b, int prec, int K, int jac,
   hipGraphExec_t exec;
   SEM_HIP(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
   SEM_HIP(hipGraphDestroy(graph));
-  b->graphs.push_back({prec, K, jac, mode, par, ver, exec});
-  return exec;
+  b->graphs.push_back({prec, K, jac, mode, par, ver, par_out, exec});
+  return b->graphs.back();
 }
 
 // rebuild the iteration kernels' lists from the solves still running
@@ -1590,8 +1593,9 @@ static bool run_cg(sem_batch *b, int prec, int jac, const sem_solve_opts *o,
     }
     if (mode == 0) maybe_compact(b);
     if (o->use_graph) {
-      SEM_HIP(hipGraphLaunch(get_graph(b, prec, K, jac, mode), b->s));
-      b->par ^= K & 1;
+      const sem_batch::GraphEntry &g = get_graph(b, prec, K, jac, mode);
+      SEM_HIP(hipGraphLaunch(g.exec, b->s));
+      b->par = g.par_out;
     } else {
       iterations(b, prec, K, jac, mode);
     }
