@@ -312,14 +312,16 @@ sem_status sem_batch_create(sem_handle *const *handles, int32_t n,
 sem_status sem_batch_destroy(sem_batch *b);
 /* Autotuner of the batched operator of section 4.2.1 (the paper's own
  * measurements compare kernel tuning choices per platform, section 4.2.3):
- * times the batched operator kernel of precision p for every
+ * times the batched operator kernel of precision p, in the form that an
+ * iteration of this batch runs it, for every
  * workgroup size (64, 128, 256 threads) that holds the (N+1)^2 columns of
  * an element of the batch's largest order (one thread per column: N = 8
  * needs 128 or 256) and every persistent grid (1 tile per workgroup, or 4,
  * 8, 16, 32 workgroups per compute unit) and keeps the fastest for later
  * solves.  With the environment variable SEM_AUTOTUNE_CACHE naming a JSON
  * file, results are read from / added to it, keyed by GPU architecture,
- * order set, precision and size bucket; a cached block size too small for
+ * order set, precision, size bucket and form (entries of earlier files,
+ * which name no form, are kept and not read); a cached block size too small for
  * the batch is ignored and tuned again.  Outputs may be NULL; *us is -1
  * when the value came from the cache. */
 sem_status sem_batch_tune(sem_batch *b, int32_t p, int32_t *block_size,

@@ -1297,6 +1297,18 @@ static void launch_alpha(sem_batch *b, bool fused) {
                      it_vbeg(b), part);
 }
 
+// The form of an iteration: whether the direction and x are updated inside the
+// two passes, whether those add the partial sums and the energies, and the
+// operator's mode
+struct IterationForm {
+  bool fused, redp, rede;
+  int mode() const { return !fused ? 3 : redp ? 2 : 1; }
+};
+static IterationForm iteration_form(const sem_batch *b, int prec) {
+  const bool fused = stream_vectors(b, prec == SEM_FP64 ? 8 : 4, factor_bytes(prec)) == 0;
+  return {fused, fused && reduce_parts(b), fused && reduce_energies(b)};
+}
+
 // One iteration (see the head of this file); last: no iteration follows in
 // this launch sequence, so that beta and the convergence flag are brought up
 // to date for the host.  The state's sums go to the same bits whichever
@@ -1308,10 +1320,10 @@ static void iteration_t(sem_batch *b, int prec, int jac, bool last) {
   double *part = b->part.as<double>();
   const VecItem *vi = it_vitems(b);
   const int nv = it_nvi(b), n = b->n;
-  const bool fused = stream_vectors(b, sizeof(TV), factor_bytes(prec)) == 0;
-  const bool redp = fused && reduce_parts(b), rede = fused && reduce_energies(b);
+  const IterationForm f = iteration_form(b, prec);
+  const bool fused = f.fused, redp = f.redp, rede = f.rede;
   const int form = !fused ? 0 : rede ? 2 : 1;
-  bax(b, prec, fused ? VZ : VP, !fused ? 3 : redp ? 2 : 1);
+  bax(b, prec, fused ? VZ : VP, f.mode());
   if (!rede)
     launch_alpha(b, fused);
   if (n == 1)
@@ -2036,7 +2048,7 @@ void drop_graphs(sem_handle *h) {
 }
 
 // --------------------------------------------------------------------------
-// autotuner: time the batched operator for each block size and persistent
+// autotuner: time the iteration's batched operator for each block size and persistent
 // grid, keep the fastest per precision; results cached in a JSON file named
 // by the SEM_AUTOTUNE_CACHE environment variable (if set)
 // --------------------------------------------------------------------------
@@ -2050,8 +2062,9 @@ static std::string tune_key(const sem_batch *b, int prec) {
   (void)hipGetDevice(&dev);
   (void)hipGetDeviceProperties(&p, dev);
   std::ostringstream k;
+  // (entries without a form are of tunings that timed the operator alone)
   k << p.gcnArchName << "|set" << b->nset << "|prec" << prec << "|log2nodes"
-    << bucket;
+    << bucket << "|form" << iteration_form(b, prec).mode();
   std::string s = k.str();
   for (auto &c : s)
     if (c == '"' || c == '\\' || c == ':') c = '_';
@@ -2109,9 +2122,22 @@ void batch_tune(sem_batch *b, int prec, int *best_bs, int *best_gm,
       return;
     }
   }
-  // operator input: the p vectors hold whatever they hold; timing only
-  std::vector<int> all(b->n, 1), mx(b->n, 1);
-  upload_active(b, all, mx);
+  // the operator in the form an iteration of this batch runs it, in a state in
+  // which every solve goes on (the sums are zero, beta is 0); the vectors hold
+  // whatever they hold
+  const IterationForm form = iteration_form(b, prec);
+  auto apply = [&] { bax(b, prec, form.fused ? VZ : VP, form.mode()); };
+  CgState running{};
+  running.rz = running.bb = 1.0;
+  running.tol2 = -1.0;
+  running.maxit = INT32_MAX;
+  running.ready = form.redp ? 0 : 1;
+  for (int q = 0; q < b->n; ++q) b->host_st[q] = running;
+  SEM_HIP(hipMemcpyAsync(b->st.p, b->host_st, b->n * sizeof(CgState), hipMemcpyHostToDevice,
+                         b->s));
+  SEM_HIP(hipMemsetAsync(b->part.p, 0, 3 * (size_t)b->n_vi * sizeof(double), b->s));
+  SEM_HIP(hipStreamSynchronize(b->s));
+  b->par = 0;
   const int bss[3] = {64, 128, 256};
   const int gms[5] = {0, 4, 8, 16, 32};
   double best = 1e300;
@@ -2121,10 +2147,10 @@ void batch_tune(sem_batch *b, int prec, int *best_bs, int *best_gm,
     for (int gm : gms) {
       b->bs[prec] = bs;
       b->gmul[prec] = gm;
-      bax(b, prec, VP, 0);  // warm
+      apply();  // warm
       SEM_HIP(hipEventRecord(b->ev0, b->s));
       const int reps = 3;
-      for (int r = 0; r < reps; ++r) bax(b, prec, VP, 0);
+      for (int r = 0; r < reps; ++r) apply();
       SEM_HIP(hipEventRecord(b->ev1, b->s));
       SEM_HIP(hipEventSynchronize(b->ev1));
       float ms = 0;
