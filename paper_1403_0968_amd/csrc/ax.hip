@@ -66,8 +66,17 @@ static void launch_reg(int64_t E, const void *D, const void *G, const void *H,
 template <int N1, class TU, class TG, class TW, class TC, bool MASS>
 static void launch_mass(int64_t E, const void *D, const void *G, const void *H,
                         const void *u, void *w, hipStream_t s) {
-  const AxRegime reg = ax_regime(
-      E * N1 * N1 * N1, (int)((MASS ? 7 : 6) * sizeof(TG) + sizeof(TU) + sizeof(TW)));
+  const int64_t nodes = E * N1 * N1 * N1;
+  const int node_bytes = (int)((MASS ? 7 : 6) * sizeof(TG) + sizeof(TU) + sizeof(TW));
+  AxRegime reg = ax_regime(nodes, node_bytes);
+  // At n1 = 8, where the hint costs no partial lines, the streaming forms are
+  // faster between the L2s' and half the last-level cache's size (FP64 58 MB
+  // 12.7 -> 11.9 us, 83 MB 18.1 -> 17.8; FP32 64 MB 12.9 -> 11.3, 90 MB 16.6 ->
+  // 15.7, 128 MB 21.4 -> 20.8; BF16 72 MB 17.4 -> 15.5), and slower on both
+  // sides (FP64 38 MB 10.5 -> 11.4, 179 MB 32.6 -> 34.3; BF16 36 MB 9.0 -> 9.3,
+  // 144 MB 26.8 -> 27.6)
+  const double mib = (double)nodes * node_bytes / (1024.0 * 1024.0);
+  if (N1 == 8 && reg == AX_CACHED && mib > 38.0 && mib <= 130.0) reg = AX_STREAM;
   if (reg == AX_SMALL)
     launch_reg<N1, TU, TG, TW, TC, MASS, AX_SMALL>(E, D, G, H, u, w, s);
   else if (reg == AX_CACHED)
