@@ -47,7 +47,7 @@ struct CoarseTab {
 struct Learn {
   int K = 0, ni = 0, ldx = 16, ldo = 16;
   DevBuf Bd, Xk, Ml, cG, cL, Sc, O, kfeat, invkh;
-  DevBuf ep;  // flexible CG: element terms of (r, c) and (c, w), [2][E]
+  DevBuf ep;  // flexible CG: terms of (r, c) and (c, w), [2][learn_epart_count]
   CoarseTab tab{};
   const sem_mlp *mnet = nullptr;
   uint64_t mver = 0;
@@ -291,8 +291,8 @@ __global__ void __launch_bounds__(256)
 // products are sum-factorised: y = sc o (B1^T x B1^T x B1^T) r_I in three
 // contractions of one direction each, then alpha = damping M_e y, then
 // c = (B1 x B1 x B1)(sc o alpha) in three more (M = 6, Q = 3: 1.1 k instead
-// of 5.8 k multiply-adds each way).  One wave per element, persistent, no workgroup barrier: lane
-// p < M^2 owns the pencil (j, k) of M contiguous interior nodes, the
+// of 5.8 k multiply-adds each way).  One wave per element; the waves of a workgroup meet only
+// to add their dot product terms (FUSE).  Lane p < M^2 owns the pencil (j, k) of M contiguous interior nodes, the
 // intermediate tensors pass through the wave's LDS region, and the loads of
 // the wave's next element (its pencil values and M_e, a packed triangle of
 // K(K+1)/2 words) are issued before the current element's contractions.  (The dense form, one wave per element
@@ -305,10 +305,11 @@ constexpr int CA_WAVES = 4;
 // is the search vector z of the solve, holding dinv o r on entry; the
 // correction is added to it in place (z = dinv o r + c, as the separate
 // correction-then-sum order gives: c is rounded to FP32 first), and every
-// element stores its terms of the two dot products that involve c,
-// epart[e] = (r_I, c) and epart[E + e] = (c, w_I), with w_I the element's
-// interior values of the operator output wL (single copies: the assembled
-// values), summed by a fixed butterfly over the wave.
+// workgroup stores the terms of its CA_WAVES elements of the two dot products
+// that involve c, epart[b] = (r_I, c) and epart[blocks + b] = (c, w_I), with
+// w_I the elements' interior values of the operator output wL (single copies:
+// the assembled values): summed by a fixed butterfly over each wave, then the
+// waves in order.
 template <class TV, bool UNIQUE, int M, int Q, bool FUSE = false>
 __global__ void __launch_bounds__(64 * CA_WAVES)
     k_coarse_apply(int64_t E, Box box, CoarseTab tb, const float *__restrict__ scg,
@@ -714,7 +715,7 @@ static void ensure_learn(sem_handle *h) {
     L->cG.alloc((size_t)h->nG * 4);
     SEM_HIP(hipMemset(L->cG.p, 0, (size_t)h->nG * 4));  // faces stay zero
     L->cL.alloc((size_t)h->nL * 4);
-    L->ep.alloc((size_t)h->E * 2 * sizeof(double));
+    L->ep.alloc((size_t)learn_epart_count(h) * 2 * sizeof(double));
     L->O.alloc((size_t)h->E * L->ldo * 4);
     L->exact_damp_dev.alloc(sizeof(float));
     kappa_features(h, L->kfeat, L->invkh);

@@ -1347,8 +1347,8 @@ static void iteration_t(sem_batch *b, int prec, int jac, bool last) {
 // flexible CG with the learned correction (single solves): (p, A p) from the
 // operator's element energies; the r update forms the assembled w, z = dinv r
 // and the partials of (r, z), (z, w), (r, r); the correction step adds c to
-// z on the element interiors and stores the element terms of (r, c) and
-// (c, w)
+// z on the element interiors and stores a term of (r, c) and of (c, w) per
+// workgroup of elements
 template <class TV, class TD>
 static void iteration_fcg_t(sem_batch *b, int prec) {
   CgState *st = b->st.as<CgState>();
