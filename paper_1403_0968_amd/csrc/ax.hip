@@ -219,9 +219,11 @@ static void launch_bax_bs(int nset, const BatchSolve *sds, CgState *st,
     fail(SEM_ERR_ARG, "batched operator: block size below n1^2 of an order");
   // order sets compiled: one order (n1 = 2..9) or the mixed set {4, 6, 8}
   switch (nset) {
-#define SEM_BAX(...)                                                                      \
+#define SEM_BAX_SET(...)                                                                  \
   launch_bax_set<BS, TV, TG, TC, DIR, STREAM, __VA_ARGS__>(sds, st, items, nitems, grid, src, \
-                                                           bd, s);                        \
+                                                           bd, s)
+#define SEM_BAX(...)        \
+  SEM_BAX_SET(__VA_ARGS__); \
   break
     case 2: SEM_BAX(2);
     case 3: SEM_BAX(3);
@@ -230,9 +232,12 @@ static void launch_bax_bs(int nset, const BatchSolve *sds, CgState *st,
     case 6: SEM_BAX(6);
     case 7: SEM_BAX(7);
     case 8: SEM_BAX(8);
-    case 9: SEM_BAX(9);
+    case 9:
+      if constexpr (BS >= 81) SEM_BAX_SET(9);  // (smaller blocks are refused above)
+      break;
     case AX_SET_468: SEM_BAX(4, 6, 8);
 #undef SEM_BAX
+#undef SEM_BAX_SET
     default: fail(SEM_ERR_ARG, "batched operator: unsupported set of orders");
   }
 }
@@ -268,10 +273,13 @@ void launch_bax(int prec, int bs, int nset, const BatchSolve *sds, CgState *st,
                 const AxItem *items, int nitems, int grid, int src, const BaxDir &bd,
                 hipStream_t s) {
   if (nitems <= 0) return;
-  if (bd.mode == 0)
-    bd.stream ? launch_bax_d<0, true>(prec, bs, nset, sds, st, items, nitems, grid, src, bd, s)
-              : launch_bax_d<0, false>(prec, bs, nset, sds, st, items, nitems, grid, src, bd, s);
-  else if (bd.mode == 1)
+  if (bd.mode == 0) {
+    // the residuals: FP64
+    if (prec != SEM_FP64) fail(SEM_ERR_ARG, "batched operator: FP64 outside an iteration");
+    auto go = bd.stream ? launch_bax_t<double, double, double, 0, true>
+                        : launch_bax_t<double, double, double, 0, false>;
+    go(bs, nset, sds, st, items, nitems, grid, src, bd, s);
+  } else if (bd.mode == 1)
     bd.stream ? launch_bax_d<1, true>(prec, bs, nset, sds, st, items, nitems, grid, src, bd, s)
               : launch_bax_d<1, false>(prec, bs, nset, sds, st, items, nitems, grid, src, bd, s);
   else if (bd.mode == 2)

@@ -6,13 +6,13 @@
 // kernel first has to fetch its work item and the solve's descriptor, a
 // chain of dependent loads that cost ~25 % of the operator time at 32^3,
 // N = 7 (measured with and without the gather: the gather itself costs
-// nothing in FP64).  Workgroup shapes and load hints as the standalone
-// operator (OpShape).  A mesh with
-// a mass term passes H = alpha(X) B and the kernel adds H o u.  With edot
-// non-null the kernel also stores every element's energy p_e^T w_e (the
-// element terms of (p, A p), in an order fixed by the node indices).
+// nothing in FP64).  A mesh with a mass term passes H = alpha(X) B and the
+// kernel adds H o u.  Inside an iteration (DIR 1 to 3) the kernel also stores
+// every element's energy p_e^T w_e (the element terms of (p, A p), in an order
+// fixed by the node indices); outside (DIR 0, the residuals) it runs in FP64.
 // Workgroup shapes, load hints and the numbering of the element blocks over
-// the XCDs: OpShape.  NTW (a solve whose vectors exceed the last-level cache):
+// the XCDs: OpShape with SOLVE, which differ from the standalone operator's.
+// NTW (a solve whose vectors exceed the last-level cache):
 // the output is stored non-temporally: 188 -> 182 us FP64 at 32^3, N = 7, and
 // the assembly that reads it next got faster too (FP32 56 -> 52 us).
 #include "ax_tile.h"
@@ -68,10 +68,14 @@ static void launch_solve_m(const SolveAx &a, hipStream_t s) {
     launch_solve_d<N1, TV, TG, TC, MASS, false, AX_CACHED, 1>(a, s);
   else if (a.mode == 3)
     launch_solve_d<N1, TV, TG, TC, MASS, true, AX_STREAM, 3>(a, s);
-  else if (stream)
-    launch_solve_d<N1, TV, TG, TC, MASS, true, AX_STREAM, 0>(a, s);
-  else
-    launch_solve_d<N1, TV, TG, TC, MASS, false, AX_CACHED, 0>(a, s);
+  else if constexpr (sizeof(TV) == 8) {  // the residuals: FP64
+    if (stream)
+      launch_solve_d<N1, TV, TG, TC, MASS, true, AX_STREAM, 0>(a, s);
+    else
+      launch_solve_d<N1, TV, TG, TC, MASS, false, AX_CACHED, 0>(a, s);
+  } else {
+    fail(SEM_ERR_ARG, "solve: the operator outside an iteration is FP64");
+  }
 }
 
 template <int N1, class TV, class TG, class TC>
