@@ -189,9 +189,9 @@ __global__ void k_dinv(int64_t nG, const int32_t *__restrict__ off,
 
 // reduced-precision copies; at n1 = 8 the BF16 copy is column-contiguous
 // ([E][6][n1^2][n1], the layout the BF16 operator kernel reads)
-__global__ void k_cast_geom(int64_t n, int N1, const double *__restrict__ G,
+__global__ void k_cast_geom(int64_t q0, int64_t n, int N1, const double *__restrict__ G,
                             float *__restrict__ G32, uint16_t *__restrict__ G16) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t q = q0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= n) return;
   const float f = (float)G[q];
   G32[q] = f;
@@ -317,10 +317,14 @@ void device_setup(sem_handle *h, const sem_mesh_desc *d, hipStream_t s) {
                      h->gmask.as<uint8_t>(), h->diag_L.as<double>(),
                      h->dinv_G.as<double>(), h->dinv_G32.as<float>());
   SEM_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_cast_geom, dim3((unsigned)((nGeo + T - 1) / T)), dim3(T),
-                     0, s, nGeo, N1, h->G64.as<double>(), h->G32.as<float>(),
-                     h->G16.as<uint16_t>());
-  SEM_HIP(hipGetLastError());
+  // (six factors a node: pieces of fewer than the 2^32 threads of a launch)
+  constexpr int64_t PIECE = (int64_t)1 << 31;
+  for (int64_t q0 = 0; q0 < nGeo; q0 += PIECE) {
+    const int64_t n = std::min(nGeo - q0, PIECE);
+    hipLaunchKernelGGL(k_cast_geom, dim3((unsigned)((n + T - 1) / T)), dim3(T), 0, s, q0, nGeo,
+                       N1, h->G64.as<double>(), h->G32.as<float>(), h->G16.as<uint16_t>());
+    SEM_HIP(hipGetLastError());
+  }
   std::vector<double> mj(gb);
   SEM_HIP(hipMemcpyAsync(mj.data(), minj.p, gb * sizeof(double),
                          hipMemcpyDeviceToHost, s));
