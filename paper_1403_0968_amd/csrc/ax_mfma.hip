@@ -27,6 +27,8 @@
 // per (i,j) column, and the fluxes are rounded to BF16 for the MFMAs.  With a
 // mass term the lumped H o u (H = alpha(X) B in BF16) is added in FP32 as the
 // result leaves LDS.
+#include <algorithm>
+
 #include "ax_tile.h"
 
 namespace sem {
@@ -37,6 +39,8 @@ typedef float mf32x4 __attribute__((ext_vector_type(4)));
 typedef float mf32x4_u __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int MW = 4;  // waves (elements) per workgroup
+// elements per launch, a wave each: a launch holds fewer than 2^32 threads
+constexpr int64_t MFMA_PIECE = (int64_t)1 << 25;
 
 struct alignas(16) MfmaLds {
   uint16_t u[512];                  // u (BF16), or the high term of its split
@@ -511,12 +515,11 @@ __global__ void __launch_bounds__(64 * MW)
 template <bool SPLIT>
 static void launch_ax_mfma_s(int N, int64_t E, const uint16_t *Dhi,
                              const uint16_t *Dlo, const uint16_t *G,
-                             const uint16_t *H, const uint16_t *u, float *w,
+                             const uint16_t *H, const uint16_t *u, float *w, int nt,
                              hipStream_t s) {
   const int64_t blocks = (E + MW - 1) / MW;
   if (blocks == 0) return;
   const dim3 grid((unsigned)blocks), block(64 * MW);
-  const int nt = ax_regime(E * (N + 1) * (N + 1) * (N + 1), 18) == AX_STREAM;
   switch (N) {
 #define SEM_AXM(NN)                                                          \
   case NN:                                                                   \
@@ -543,11 +546,14 @@ static void launch_ax_mfma_s(int N, int64_t E, const uint16_t *Dhi,
 void launch_ax_mfma(int N, bool split, int64_t E, const uint16_t *Dhi,
                     const uint16_t *Dlo, const uint16_t *G, const uint16_t *H,
                     const uint16_t *u, float *w, hipStream_t s) {
-  if (split)
-    launch_ax_mfma_s<true>(N, E, Dhi, Dlo, G, H, u, w, s);
-  else
-    launch_ax_mfma_s<false>(N, E, Dhi, Dlo, G, H, u, w, s);
-  SEM_HIP(hipGetLastError());
+  const int64_t N3 = (int64_t)(N + 1) * (N + 1) * (N + 1);
+  const int nt = ax_regime(E * N3, 18) == AX_STREAM;
+  for (int64_t e = 0; e < E; e += MFMA_PIECE) {
+    const int64_t n = std::min(E - e, MFMA_PIECE);
+    auto go = split ? launch_ax_mfma_s<true> : launch_ax_mfma_s<false>;
+    go(N, n, Dhi, Dlo, G + 6 * e * N3, H ? H + e * N3 : nullptr, u + e * N3, w + e * N3, nt, s);
+    SEM_HIP(hipGetLastError());
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -723,7 +729,7 @@ __global__ void __launch_bounds__(64 * MW) __attribute__((amdgpu_waves_per_eu(3)
 // solve's workgroups return at once.
 template <int N1, bool SPLIT>
 __global__ void __launch_bounds__(64 * MW)
-    k_ax_mfma_solve(int64_t E, const uint16_t *__restrict__ Dhi,
+    k_ax_mfma_solve(int64_t e0, int64_t E, const uint16_t *__restrict__ Dhi,
                     const uint16_t *__restrict__ Dlo, const uint16_t *__restrict__ G,
                     const uint16_t *__restrict__ H, const float *__restrict__ z,
                     float *__restrict__ w, Box box, DirArgs<float> da, int mode, int nt,
@@ -735,11 +741,11 @@ __global__ void __launch_bounds__(64 * MW)
   dir.p = (gp<const float>)da.p;
   dir.pnew = (gp<float>)da.pnew;
   if (dir_mfma(da.st, mode, da.part, da.stride, da.beg, da.end,
-               blockIdx.x == 0 && threadIdx.x == 0, dir))
+               e0 == 0 && blockIdx.x == 0 && threadIdx.x == 0, dir))
     return;  // uniform: the solve has ended
   m16x4 fh, fl, bh, bl;
   d_operands<N1>(l, Dhi, Dlo, fh, fl, bh, bl);
-  const int64_t e = (int64_t)blockIdx.x * MW + wv;
+  const int64_t e = e0 + (int64_t)blockIdx.x * MW + wv;
   solve_elem_mfma<N1, SPLIT>(l, lds[wv], e, e < E, nt != 0, box, dir, (gp<float>)w, G,
                              (gp<const uint16_t>)H, fh, fl, bh, bl, (gp<double>)edot);
 }
@@ -830,7 +836,7 @@ __global__ void __launch_bounds__(64 * MW9) __attribute__((amdgpu_waves_per_eu(2
 // the single-solve operator at n1 = 9 (as k_ax_mfma_solve)
 template <bool SPLIT>
 __global__ void __launch_bounds__(64 * MW9)
-    k_ax_mfma_solve9(int64_t E, const uint16_t *__restrict__ Dhi,
+    k_ax_mfma_solve9(int64_t e0, int64_t E, const uint16_t *__restrict__ Dhi,
                      const uint16_t *__restrict__ Dlo, const uint16_t *__restrict__ G,
                      const uint16_t *__restrict__ H, const float *__restrict__ z,
                      float *__restrict__ w, Box box, DirArgs<float> da, int mode, int nt,
@@ -842,11 +848,11 @@ __global__ void __launch_bounds__(64 * MW9)
   dir.p = (gp<const float>)da.p;
   dir.pnew = (gp<float>)da.pnew;
   if (dir_mfma(da.st, mode, da.part, da.stride, da.beg, da.end,
-               blockIdx.x == 0 && threadIdx.x == 0, dir))
+               e0 == 0 && blockIdx.x == 0 && threadIdx.x == 0, dir))
     return;  // uniform: the solve has ended
   m16x4 fh, fl, bh, bl;
   d_operands9(l, Dhi, Dlo, fh, fl, bh, bl);
-  const int64_t e = (int64_t)blockIdx.x * MW9 + wv;
+  const int64_t e = e0 + (int64_t)blockIdx.x * MW9 + wv;
   solve_elem_mfma9<SPLIT>(l, lds[wv], e, e < E, box, dir, (gp<float>)w, G,
                           (gp<const uint16_t>)H, fh, fl, bh, bl, (gp<double>)edot);
 }
@@ -862,10 +868,13 @@ void launch_ax_mfma_solve(const SolveAx &a, hipStream_t s) {
                              a.nparts,           0,
                              a.nparts};
   auto go = [&](auto kernel, int waves) {
-    hipLaunchKernelGGL(kernel, dim3((unsigned)((a.E + waves - 1) / waves)), dim3(64 * waves),
-                       0, s, a.E, (const uint16_t *)a.D, (const uint16_t *)a.Dlo,
-                       (const uint16_t *)a.G, (const uint16_t *)a.H, (const float *)a.u,
-                       (float *)a.w, a.box, da, a.mode, nt, a.edot);
+    for (int64_t e0 = 0; e0 < a.E; e0 += MFMA_PIECE) {
+      const int64_t n = std::min(a.E - e0, MFMA_PIECE);
+      hipLaunchKernelGGL(kernel, dim3((unsigned)((n + waves - 1) / waves)), dim3(64 * waves), 0,
+                         s, e0, a.E, (const uint16_t *)a.D, (const uint16_t *)a.Dlo,
+                         (const uint16_t *)a.G, (const uint16_t *)a.H, (const float *)a.u,
+                         (float *)a.w, a.box, da, a.mode, nt, a.edot);
+    }
   };
   switch (n1) {
 #define SEM_AXMS(NN)                          \
