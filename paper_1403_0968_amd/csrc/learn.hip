@@ -243,6 +243,11 @@ __global__ void __launch_bounds__(64)
     xp[q] = q < 8 ? f32_to_bf16(kf[e * 8 + q]) : (uint16_t)0;
 }
 
+// threads per element of the kernels that fill its packed triangle: four waves
+// for K = 27, one for the small ones, whose meshes may have 2^24 elements and
+// more (a launch holds fewer than 2^32 threads)
+static int tri_threads(int K) { return K * (K + 1) / 2 > 64 ? 256 : 64; }
+
 // element operators from the network outputs: M_e = invkh_e L L^T, packed
 // lower triangle (entry (a, b) and (b, a) are the same sum of the same
 // products, so one copy loses nothing)
@@ -253,7 +258,7 @@ __global__ void __launch_bounds__(256)
   const float *o = O + e * ldo;
   const float sc = invkh[e];
   const int kp = K * (K + 1) / 2;
-  for (int ab = threadIdx.x; ab < kp; ab += 256) {  // packed row a, column b <= a
+  for (int ab = threadIdx.x; ab < kp; ab += (int)blockDim.x) {  // packed row a, column b <= a
     int a = 0;
     while ((a + 1) * (a + 2) / 2 <= ab) ++a;
     const int b = ab - a * (a + 1) / 2;
@@ -273,7 +278,7 @@ __global__ void __launch_bounds__(256)
   const double *M = Mex + e * K * K;
   const double sc = (double)invkh[e];
   const int kp = K * (K + 1) / 2;
-  for (int ab = threadIdx.x; ab < kp; ab += 256) {
+  for (int ab = threadIdx.x; ab < kp; ab += (int)blockDim.x) {
     int a = 0;
     while ((a + 1) * (a + 2) / 2 <= ab) ++a;
     const int b = ab - a * (a + 1) / 2;
@@ -745,7 +750,7 @@ void learn_refresh(sem_handle *h) {
   if (ldx_net != L->ldx) fail(SEM_ERR_STATE, "learned correction: input width");
   mlp_forward(net, L->Xk.as<uint16_t>(), L->ldx, (int)h->E, L->O.as<float>(),
               L->ldo, 0);
-  hipLaunchKernelGGL(k_factor_to_M, dim3((unsigned)h->E), dim3(256), 0, 0, h->E,
+  hipLaunchKernelGGL(k_factor_to_M, dim3((unsigned)h->E), dim3(tri_threads(L->K)), 0, 0, h->E,
                      L->K, L->O.as<float>(), L->ldo, L->invkh.as<float>(),
                      L->Ml.as<float>());
   SEM_HIP(hipGetLastError());
@@ -903,7 +908,7 @@ void learn_attach_exact(sem_handle *h, double damping) {
   DevBuf Mex;
   Mex.alloc((size_t)h->E * L->K * L->K * 8);
   coarse_exact(h, L, Mex.as<double>(), 0);
-  hipLaunchKernelGGL(k_exact_to_M, dim3((unsigned)h->E), dim3(256), 0, 0, h->E,
+  hipLaunchKernelGGL(k_exact_to_M, dim3((unsigned)h->E), dim3(tri_threads(L->K)), 0, 0, h->E,
                      L->K, Mex.as<double>(), L->invkh.as<float>(), L->Ml.as<float>());
   SEM_HIP(hipGetLastError());
   const float f = (float)damping;
