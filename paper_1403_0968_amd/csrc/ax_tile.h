@@ -59,8 +59,9 @@ template <int N1, class TC = double> constexpr int lds_words(int epb) {
 //  * AX_SMALL, at most 0.2M local nodes: the fewest elements that fill a wave,
 //    so that the mesh spreads over the compute units (FP64 N = 7, 0.1M nodes
 //    6.6 -> 5.2 us against four elements per workgroup).
-//  * AX_CACHED, the arrays that come round again fit the last-level cache:
-//    256 MiB of what one application of the standalone operator moves, or of
+//  * AX_CACHED, the arrays that come round again fit the last-level cache (at
+//    n1 = 8 in the standalone operator without a band in the middle,
+//    launch_mass in ax.hip): 256 MiB of what one application of the standalone operator moves, or of
 //    a solve's operator and vectors (24^3, N = 7, FP32 flexible CG at 314 MB:
 //    137 ms a solve with the streaming forms, 152 ms with these): no streaming
 //    hints, which would make the next application miss (FP64 N = 7, 4M nodes
@@ -299,6 +300,8 @@ __device__ __forceinline__ void ax_tile(int t, int64_t e0, int64_t E,
                          : Ge[q * N3 + k * NP];
   }
 
+  // (the mass factor is read with the streaming hint in every size class: the
+  // rule of the factors, NTG, is not applied to it)
   TG hm[MASS ? N1 : 1];
   if constexpr (MASS) {
 #pragma unroll

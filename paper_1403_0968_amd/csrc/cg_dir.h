@@ -15,10 +15,12 @@
 // passes run at the memory's rate and the fused one is slower (FP64, 32^3,
 // N = 7: operator 179 -> 212 us, r update 83 -> 136 us, against 66 us for
 // the p and x pass).  In the caches the launches and their latency bound the
-// iteration.  Solve times, five launches against two: FP64 4^3 N = 4 2.06 -> 1.34 ms, BF16 refinement 15 x 11 x 13
-// N = 7 37.1 -> 29.5 ms (27 -> 22 us per iteration); with the coarse
-// correction at 24^3, N = 7, FP32 (where beta has its own kernel) 151 -> 148
-// ms.  Results are the same bits.
+// iteration.  Solve times, five launches against two: FP64 4^3 N = 4 2.06 ->
+// 1.34 ms, BF16 refinement 15 x 11 x 13 N = 7 37.1 -> 29.5 ms (27 -> 22 us per
+// iteration); with the coarse correction at 24^3, N = 7, FP32 (where beta has
+// its own kernel) 151 -> 148 ms.  (With the operator's size classes since: 1.27
+// and 29.1 ms, and 133 ms with fewer terms in beta's kernel.)  Results are the
+// same bits.
 //
 // Scalars are split so that no kernel writes what its other workgroups
 // read: the operator reads the main fields of CgState and its first

@@ -890,7 +890,10 @@ struct sem_batch {
   // operator block size per precision: 256 threads hold about the elements per
   // workgroup that the single-solve operator takes (OpShape); FP32 operator of
   // 24 solves of 11.6M nodes, N in {3, 5, 7}: 64, 128 and 256 threads 94, 90
-  // and 84 us
+  // and 84 us.  Whole solves of 23 batches (2 to 64 solves of 3^3 to 48^3, every
+  // order) in each precision against 128 / 64 / 64 threads and the five-launch
+  // form: none slower, 2 of 4^3, N = 4 2.44 -> 1.67 ms (FP64), 8 of 4^3, N = 7
+  // 2.73 -> 1.93 (BF16), 9 of 12^3, N = 7 20.9 -> 18.8 (FP64)
   int bs[5] = {256, 256, 256, 256, 256};
   int gmul[5] = {0, 0, 0, 0, 0};  // persistent grid = 256 CUs x gmul (0: 1 item/WG)
   sem::CgState *host_st = nullptr;
