@@ -61,15 +61,15 @@ template <int N1, class TC = double> constexpr int lds_words(int epb) {
 //    6.6 -> 5.2 us against four elements per workgroup).
 //  * AX_CACHED, the arrays that come round again fit the last-level cache (at
 //    n1 = 8 in the standalone operator without a band in the middle,
-//    launch_mass in ax.hip): 256 MiB of what one application of the standalone operator moves, or of
-//    a solve's operator and vectors (24^3, N = 7, FP32 flexible CG at 314 MB:
-//    137 ms a solve with the streaming forms, 152 ms with these): no streaming
-//    hints, which would make the next application miss (FP64 N = 7, 4M nodes
-//    44.3 -> 40.7 us, 5.2M nodes 58.2 -> 63.4; FP32 N = 7, 8M nodes 40.6 -> 38.1;
-//    BF16 N = 1, 2M nodes 20.1 -> 6.4), and in the solvers element blocks
-//    numbered so that every XCD takes one contiguous run of them (XCD):
-//    neighbours share the gathered vector's lines in one L2 (FP64 N = 6, 2.4M
-//    nodes 51.2 -> 41.6 us, FP32 N = 7, 2.5M 29.5 -> 20.5).
+//    launch_mass in ax.hip): 256 MiB of what one application of the standalone
+//    operator moves, or of a solve's operator and vectors (24^3, N = 7, FP32
+//    flexible CG at 314 MB: 137 ms a solve with the streaming forms, 152 ms with
+//    these): no streaming hints, which would make the next application miss
+//    (FP64 N = 7, 4M nodes 44.3 -> 40.7 us, 5.2M nodes 58.2 -> 63.4; FP32 N = 7,
+//    8M nodes 40.6 -> 38.1; BF16 N = 1, 2M nodes 20.1 -> 6.4), and in the
+//    solvers element blocks numbered so that every XCD takes one contiguous run
+//    of them (XCD): neighbours share the gathered vector's lines in one L2 (FP64
+//    N = 6, 2.4M nodes 51.2 -> 41.6 us, FP32 N = 7, 2.5M 29.5 -> 20.5).
 //  * AX_STREAM: the factors are read with the streaming hint only where a
 //    factor column of a wave's load covers whole cache lines (n1 = 8; n1 = 4
 //    in FP64; in the standalone operator also the other orders of NTG below).
