@@ -48,11 +48,12 @@ constexpr int FD_RMAX = 7;
 //   * 256 x 8 up to 1.5M nodes, and up to 3M threads (r <= 2: 2.5M) where the
 //     grid is at least 64 tall (r = 7, 1024^2 23.4 -> 10.2, 1500^2 27.3 -> 21.1;
 //     187500 x 16 is slower with it, 20.4 -> 23.0);
-//   * 256 x 8 on larger grids for r <= 4 where the strips are a multiple of 8:
-//     a strip's chunks then run on one XCD, whose L2 holds the 2r rows that
-//     chunks share (8192^2, r = 1, 2, 3, 4 263, 263, 267, 270 -> 259, 256, 257,
-//     265, 16384 x 1024, r = 3 78 -> 64; 20 strips, 5000 x 3000 60, 62, 65, 67
-//     -> 62, 66, 70, 73);
+//   * 256 x 8 on larger grids for r <= 4 (beyond 50M nodes r <= 3) where the
+//     strips are a multiple of 8: a strip's chunks then run on one XCD, whose L2
+//     holds the 2r rows that chunks share (8192^2, r = 1, 2, 3 263, 263, 268 ->
+//     259, 255, 258, in place r = 4 270 -> 274; 4096^2, r = 4 72 -> 65,
+//     16384 x 1024, r = 3 78 -> 64; 20 strips, 5000 x 3000, r = 1, 2, 3, 4 60, 62,
+//     65, 67 -> 62, 66, 70, 73);
 //   * 256 x 16 up to 5.2M threads from 32 rows, and up to 12M nodes from
 //     1024 x 512 (3000^2, r = 3, 5, 7 42.8, 49.1, 58.9 -> 41.3, 46.3, 55.8;
 //     80000 x 100, r = 7 is slower with it, 44.3 -> 47.4);
@@ -76,7 +77,7 @@ static FdShape fd_shape(int64_t nx, int64_t ny, int r) {
   FdShape sh = {256, r <= 2 ? (large ? 8 : 16) : large && r <= 4 ? 16 : 32};
   if (nx <= 64 || nodes <= 700000)
     sh = {64, 4};
-  else if (nodes <= 1500000 || (r <= 4 && strips % 8 == 0 && ny >= 512) ||
+  else if (nodes <= 1500000 || (r <= (large ? 3 : 4) && strips % 8 == 0 && ny >= 512) ||
            (ny >= 64 && threads <= (r <= 2 ? 2500000 : 3000000)))
     sh = {256, 8};
   else if ((ny >= 32 && threads <= 5200000) ||

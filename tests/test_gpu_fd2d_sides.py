@@ -26,7 +26,8 @@ def _step(w, r, c, cur, prev):
                                      (24001, 63, 6), (24001, 64, 6), (1000, 5070, 7),
                                      (1000, 5090, 7), (1023, 5500, 3), (1024, 5500, 3),
                                      (131000, 16, 7), (3000001, 5, 1),
-                                     (7001, 7201, 2), (7001, 7201, 4), (7001, 7101, 4)])
+                                     (7001, 7201, 2), (7001, 7201, 4), (7001, 7101, 4),
+                                     (8192, 6105, 4), (8192, 6103, 4), (8192, 6105, 3)])
 def test_sides(nx, ny, r):
     from paper_1403_0968_amd import sem
     t = torch()
