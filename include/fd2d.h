@@ -42,8 +42,8 @@ sem_status fd2d_weights(int32_t r, double *w);
  * u_next from u_cur (time level n) and u_prev (level n-1),
  * each nx * ny doubles.  u_next may be the same buffer as u_prev (each node
  * of u_prev is read only to produce the same node of u_next) but must not
- * overlap u_cur.  nx, ny >= 1, r in 1..7, dx > 0, dt and dx finite;
- * SEM_ERR_ARG otherwise. */
+ * overlap u_cur.  nx, ny >= 1, ceil(nx / 256) ceil(ny / 32) < 2^24 (one
+ * launch), r in 1..7, dx > 0, dt and dx finite; SEM_ERR_ARG otherwise. */
 sem_status fd2d_step(const double *u_cur, const double *u_prev, double *u_next,
                      int64_t nx, int64_t ny, int32_t r, double dt, double dx,
                      void *stream);

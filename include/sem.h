@@ -399,7 +399,8 @@ sem_status sem_mlp_set_precision(sem_mlp *net, int32_t p);
 sem_status sem_mlp_get_precision(const sem_mlp *net, int32_t *p);
 /* Forward pass of the section 4.2.2 correction network on B samples:
  * X device BF16 [B][ldx] (ldx >= n_in_padded, a multiple of 16; padding
- * columns finite), Y device FP32 [B][n_out]. */
+ * columns finite), Y device FP32 [B][n_out].  Y may overlap X (the outputs
+ * then pass through the network's scratch). */
 sem_status sem_mlp_forward(sem_mlp *net, const uint16_t *X, int32_t ldx,
                            int32_t B, float *Y, void *stream);
 /* Loss and gradient of the section 4.2.2 coarse factor (n_out = K(K+1)/2,
